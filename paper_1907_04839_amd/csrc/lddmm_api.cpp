@@ -197,6 +197,7 @@ struct Job {
   size_t rb;
   int dim;   // 2 (planar) or 3
   int spt;   // records per step: 1 (Euler) or 4 (Runge-Kutta stage states)
+  int nh;    // partial sums of H0 in h0p (and hTp)
 
   // Record of stage s (0-based) of step t; (t, 0) is the state at step t.
   void* rec(int t, int s = 0) const {
@@ -211,7 +212,10 @@ struct Job {
 // The launch plan of a problem (the workspace layout depends on its S).
 Plan plan_for(const lddmm_params& p) {
   Plan plan = make_plan(p.n, target_waves());
-  if (!plan_overridden()) widen_plan(plan, p.precision, p.integrator == LDDMM_RK4);
+  if (!plan_overridden()) {
+    widen_plan(plan, p.precision, p.integrator == LDDMM_RK4);
+    plan.row = row_plan(p.n, p.precision);
+  }
   return plan;
 }
 
@@ -242,7 +246,14 @@ Job make_job(const lddmm_params& p, void* ws) {
   j.rk_acc = at<double>(ws, j.L.rk_acc);
   j.rk_lam = at<double>(ws, j.L.rk_lam);
   j.spt = p.integrator == LDDMM_RK4 ? 4 : 1;
+  j.nh = j.plan.nb;
   j.rb = rec_bytes(p.precision);
+  if (j.plan.row.m > 0) {
+    // One H0 partial per row workgroup, in the second adjoint record buffer, which
+    // nothing writes before the loss has read them.
+    j.nh = j.plan.row.groups;
+    j.h0p = j.hTp = reinterpret_cast<double*>(j.arec_buf(1));
+  }
   j.dim = p.dim == 2 ? 2 : 3;
   return j;
 }
@@ -259,6 +270,7 @@ hipError_t run_forward(const Job& j, int t0, int t1, bool first, bool store_ckpt
       FwdArgs a{};
       a.n = j.p.n; a.nb = j.plan.nb; a.S = j.plan.S; a.chunk = j.plan.chunk;
       a.wchunk = j.plan.wchunk;
+      a.ig = j.plan.row.ig; a.jg = j.plan.row.jg;
       a.dim = j.dim;
       a.rk = stages == 4 ? st + 1 : 0;
       a.rk_acc = j.rk_acc;
@@ -292,6 +304,7 @@ hipError_t run_adjoint(const Job& j, int t0, int t1, int* cur, double* grad, hip
       AdjArgs a{};
       a.n = j.p.n; a.nb = j.plan.nb; a.S = j.plan.S; a.chunk = j.plan.chunk;
       a.wchunk = j.plan.wchunk_a;
+      a.ig = j.plan.row.ig; a.jg = j.plan.row.jg;
       a.dim = j.dim;
       a.rk = stages == 4 ? st + 1 : 0;
       a.rk_lam = j.rk_lam;
@@ -353,6 +366,7 @@ lddmm_status run_grad(lddmm_ctx* ctx, const Job& j, const double* q0, const doub
             "final state copy");
     FwdArgs a{};
     a.n = n; a.nb = j.plan.nb; a.S = j.plan.S; a.chunk = j.plan.chunk; a.wchunk = j.plan.wchunk;
+    a.ig = j.plan.row.ig; a.jg = j.plan.row.jg;
     a.dim = j.dim;
     a.sc = j.sc;
     a.rec_t = j.rec(T);
@@ -365,7 +379,7 @@ lddmm_status run_grad(lddmm_ctx* ctx, const Job& j, const double* q0, const doub
     HIP_TRY(ctx, launch_fwd_step(mode, j.plan, a, s, tm->take(0)), "final energy");
   }
   const double rscale = j.spt == 4 ? j.sc.dt / 6.0 : 1.0;   // first stage adjoint: dt/6 lambda
-  HIP_TRY(ctx, launch_loss(mode, n, j.plan.nb, params->lambda, j.sc.bscale, rscale, j.st, j.xc,
+  HIP_TRY(ctx, launch_loss(mode, n, j.nh, params->lambda, j.sc.bscale, rscale, j.st, j.xc,
                            j.cen, fin ? j.hTp : j.h0p, j.ad, j.arec_buf(0), out3, q1, nullptr,
                            ctx->flag, grad_x, fin ? j.hqT : nullptr, fin ? j.hpT : nullptr, s),
           "loss");
@@ -472,7 +486,7 @@ lddmm_status lddmm_shoot_forward(lddmm_ctx* ctx, const lddmm_params* params, con
   HIP_TRY(ctx, launch_stage(params->precision, n, q0, p0, nullptr, j.cen, j.sc.k, j.st, j.xc,
                             j.rec(0), s), "stage");
   HIP_TRY(ctx, run_forward(j, 0, params->T, true, false, s, &ctx->timer), "forward step");
-  HIP_TRY(ctx, launch_forward_out(n, j.plan.nb, j.st, j.cen, j.h0p, H0, q1, p1, s), "forward out");
+  HIP_TRY(ctx, launch_forward_out(n, j.nh, j.st, j.cen, j.h0p, H0, q1, p1, s), "forward out");
   return LDDMM_OK;
 }
 
@@ -607,7 +621,7 @@ lddmm_status lddmm_flow(lddmm_ctx* ctx, const lddmm_params* params, const double
     HIP_TRY(ctx, launch_flow(params->precision, W, a, s, ctx->timer.take(2)), "point flow");
   }
   if (q1 || p1)
-    HIP_TRY(ctx, launch_forward_out(n, j.plan.nb, j.st, j.cen, j.h0p, nullptr, q1, p1, s),
+    HIP_TRY(ctx, launch_forward_out(n, j.nh, j.st, j.cen, j.h0p, nullptr, q1, p1, s),
             "forward out");
   return LDDMM_OK;
 }

@@ -20,6 +20,15 @@ enum Mode : int { kFP32 = 0, kFP32Comp = 1, kFP64 = 2 };
 // (i mod 64) of a wave of i-block ib = i / 64; the j range is split into S
 // chunks (one workgroup each) and, inside a workgroup, over W waves.
 // Partial sums of different chunks are combined in chunk order.
+// Launch of a row kernel: a workgroup of ig x jg waves takes ig groups of m
+// landmarks i against every j (each wave one group and every jg-th tile of 64
+// j), so a step needs no partial sums in memory and no second launch.
+struct RowPlan {
+  int m;        // landmarks i per wave (0: no row kernel)
+  int ig, jg;   // waves per workgroup: i-groups times shares of the j tiles
+  int groups;   // workgroups
+};
+
 struct Plan {
   int n;        // landmarks
   int nb;       // i-blocks of 64
@@ -29,6 +38,7 @@ struct Plan {
   int wchunk;   // j per wave of the forward pair kernel
   int Wa;       // waves per workgroup of the adjoint pair kernel
   int wchunk_a; // j per wave of the adjoint pair kernel
+  RowPlan row;  // m > 0: the row kernels take the step instead
 };
 
 // Coordinates enter the pair kernels pre-scaled by k = sqrt(log2(e) / (2 sigma^2)),
@@ -130,6 +140,45 @@ inline void widen_plan(Plan& p, int mode, bool rk) {
   p.wchunk = (p.chunk + wf - 1) / wf;
   p.Wa = wa;
   p.wchunk_a = (p.chunk + wa - 1) / wa;
+}
+
+// The row kernels take the sizes where a step is bound by its launches rather
+// than by its pair sums: n <= 5120 with FP32 sums, n <= 3072 in FP64.  Measured
+// per loss+gradient evaluation (us, T = 20; split kernels against row kernels):
+//   FP32-compensated: n = 200 293 -> 157; 1000 298 -> 187; 1847 339 -> 256;
+//     2500 494 -> 353; 3001 550 -> 412; 4096 658 -> 606; 5000 994 -> 907; 6000
+//     1133 -> 1207, where the split kernels' loops are the faster ones.
+//   FP64: n = 64 222 -> 140 (the split plan's one launch per step runs one
+//     workgroup); 500 375 -> 176; 1000 354 -> 233; 1847 475 -> 418; 2500 809 ->
+//     722; 3001 933 -> 839; 4096 1188 -> 1340.
+// m is chosen for the fullest CU's work, ceil(groups / 256) (m + 1): m rows and
+// about one row's time for a wave's loads, the larger m of equals.  At n = 1300
+// m = 3, 4, 5 took 219, 234, 260 us, at n = 2500 390, 372, 353; FP64 at n = 2500
+// (adjoint step) 25.7 us for m = 2 and 21.8 for m = 4.  One workgroup per CU gets 8 waves; with up to two,
+// both are merged into one, whose i-groups share their j records in the
+// CU's cache (n = 1847: 266 -> 256 us; FP64 475 -> 418).  FP64 waves hold twice
+// the registers: 8 per workgroup at most.
+inline RowPlan row_plan(int n, int mode) {
+  constexpr int kCUs = 256;   // MI355X
+  const bool f64 = mode == kFP64;
+  RowPlan r{};
+  if (n > (f64 ? 3072 : 5120)) return r;
+  const int lo = f64 ? 2 : 3, hi = f64 ? 4 : 5;
+  const auto groups = [&](int rows) { return (n + rows - 1) / rows; };
+  int best = 0;
+  for (int m = lo; m <= hi; ++m) {
+    const int load = (groups(m) + kCUs - 1) / kCUs * (m + 1);
+    if (r.m == 0 || load <= best) {
+      best = load;
+      r.m = m;
+    }
+  }
+  const int g = groups(r.m), tiles = (n + 63) / 64;
+  r.ig = g > kCUs && g <= 2 * kCUs ? 2 : 1;
+  r.jg = f64 && g > kCUs ? 4 : 8;
+  if (r.jg > tiles) r.jg = tiles;
+  r.groups = groups(r.m * r.ig);
+  return r;
 }
 
 inline Scales make_scales(double sigma, int T) {

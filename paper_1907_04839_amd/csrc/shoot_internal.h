@@ -14,6 +14,7 @@ namespace lddmm {
 // Runge-Kutta step (pair sums + update).
 struct FwdArgs {
   int n, nb, S, chunk, wchunk;
+  int ig, jg;           // row kernels: i-groups per workgroup, waves per i-group
   int dim;              // 3, or 2 for planar problems (z terms left out)
   int rk;               // 0: Euler step.  1..4: Runge-Kutta stage rk, whose pair
                         // sums are taken at the stage state in rec_t; stages
@@ -26,7 +27,7 @@ struct FwdArgs {
   double* st;           // FP64 state [6][n]: q (3 rows) then p (3 rows), centred
   double* hp0;          // [3][n]: Hp(q0,p0) (written at t == 0, else null)
   double* hq0;          // [3][n]: Hq(q0,p0) (optional, with hp0)
-  double* h0_part;      // [nb]: per i-block sum p0.Hp0 (t == 0, else null)
+  double* h0_part;      // per i-block (row kernels: per workgroup) sum p0.Hp0 (t == 0, else null)
   double* ckpt;         // [6][n]: copy of the new state (null unless a checkpoint)
   void* partial;        // [S][6][n] partial sums when S > 1
 };
@@ -35,6 +36,7 @@ struct FwdArgs {
 // adjoint of a Runge-Kutta step.
 struct AdjArgs {
   int n, nb, S, chunk, wchunk;
+  int ig, jg;           // row kernels: i-groups per workgroup, waves per i-group
   int dim;              // 3, or 2 for planar problems
   int rk;               // 0: Euler step.  1..4: stage rk of the Runge-Kutta
                         // adjoint (taken from 4 down to 1): the pair sums give

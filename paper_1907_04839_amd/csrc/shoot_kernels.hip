@@ -300,6 +300,7 @@ __device__ __forceinline__ void block_combine_store(Acc* red, const Acc o[NC], i
 struct FwdState { double q[3], p[3], acc[6]; };
 struct AdjState { double a[3], b[3], hp0[3], hq0[3], lam[6]; };
 
+// (i is clamped: lanes without a landmark load the last one's state.)
 template <bool RKS>
 __device__ __forceinline__ FwdState load_fwd_state(const FwdArgs& A, int i) {
   FwdState v;
@@ -325,13 +326,14 @@ __device__ __forceinline__ AdjState load_adj_state(const AdjArgs& A, int i) {
   return v;
 }
 
+// Landmark i of this lane (own: it has one); part: index of the wave's H0 partial.
+// The whole wave calls it.
 template <typename R, bool RKS>
-__device__ __forceinline__ void fwd_finish(const FwdArgs& A, int ib, int lane, FwdState v,
-                                           const double hp[3], const double hqs[3]) {
+__device__ __forceinline__ void fwd_finish(const FwdArgs& A, int i, bool own, int part, int lane,
+                                           FwdState v, const double hp[3], const double hqs[3]) {
   const int n = A.n;
-  const int i = ib * 64 + lane;
   double h0 = 0.0;
-  if (i < n) {
+  if (own) {
     if (A.hp0) {
       for (int c = 0; c < 3; ++c) A.hp0[c * n + i] = hp[c];
       h0 = v.p[0] * hp[0] + v.p[1] * hp[1] + v.p[2] * hp[2];
@@ -385,22 +387,20 @@ __device__ __forceinline__ void fwd_finish(const FwdArgs& A, int ib, int lane, F
   }
   if (A.h0_part) {          // whole wave takes part: fixed butterfly order
     for (int off = 32; off > 0; off >>= 1) h0 += __shfl_xor(h0, off, 64);
-    if (lane == 0) A.h0_part[ib] = h0;
+    if (lane == 0) A.h0_part[part] = h0;
   }
 }
 
+// sa = A1 / kappa - A2 and sb = B of landmark i.
 template <typename R, bool RKS>
-__device__ __forceinline__ void adj_finish(const AdjArgs& A, int ib, int lane, AdjState v,
-                                           const double s[9]) {
+__device__ __forceinline__ void adj_finish(const AdjArgs& A, int i, AdjState v, const double sa[3],
+                                           const double sb[3]) {
   const int n = A.n;
-  const int i = ib * 64 + lane;
-  if (i >= n) return;
-  const double inv_kappa = 1.0 / A.sc.kappa;
   if constexpr (!RKS) {
     for (int c = 0; c < 3; ++c) {
-      const double Ac = A.sc.adj_a * (s[c] * inv_kappa - s[3 + c]);
+      const double Ac = A.sc.adj_a * sa[c];
       v.a[c] = v.a[c] + A.sc.dt * Ac;
-      v.b[c] = v.b[c] + A.sc.dt * s[6 + c];
+      v.b[c] = v.b[c] + A.sc.dt * sb[c];
     }
     for (int c = 0; c < 3; ++c) { A.ad[c * n + i] = v.a[c]; A.ad[(3 + c) * n + i] = v.b[c]; }
     const double bs = A.sc.bscale;
@@ -418,7 +418,7 @@ __device__ __forceinline__ void adj_finish(const AdjArgs& A, int ib, int lane, A
     const double cw = A.rk == 4 ? dt : 0.5 * dt;
     double lam[6], u[6];
     for (int c = 0; c < 3; ++c) {
-      const double wa = A.sc.adj_a * (s[c] * inv_kappa - s[3 + c]), wb = s[6 + c];
+      const double wa = A.sc.adj_a * sa[c], wb = sb[c];
       const double la = A.rk == 4 ? v.a[c] : v.lam[c], lb = A.rk == 4 ? v.b[c] : v.lam[3 + c];
       lam[c] = la + wa;
       lam[3 + c] = lb + wb;
@@ -444,6 +444,18 @@ __device__ __forceinline__ void adj_finish(const AdjArgs& A, int ib, int lane, A
     for (int c = 0; c < 3; ++c) A.grad[3 * i + c] = v.b[c] + v.hp0[c];
   if (A.grad_q0)
     for (int c = 0; c < 3; ++c) A.grad_q0[3 * i + c] = v.a[c] + v.hq0[c];
+}
+
+// The same for the lane's landmark of i-block ib from the nine sums A1, A2, B.
+template <typename R, bool RKS>
+__device__ __forceinline__ void adj_finish9(const AdjArgs& A, int ib, int lane, const AdjState& v,
+                                            const double s[9]) {
+  const int i = ib * 64 + lane;
+  if (i >= A.n) return;
+  const double inv_kappa = 1.0 / A.sc.kappa;
+  double sa[3];
+  for (int c = 0; c < 3; ++c) sa[c] = s[c] * inv_kappa - s[3 + c];
+  adj_finish<R, RKS>(A, i, v, sa, s + 6);
 }
 
 // ---------------------------------------------------------------------------
@@ -485,7 +497,7 @@ __device__ __forceinline__ void fwd_block(const FwdArgs& A, int ib, int s,
     if (w == 0) {
       double h[NC];
       for (int c = 0; c < NC; ++c) h[c] = red[c * 64 + lane];
-      fwd_finish<R, RKS>(A, ib, lane, v, h, h + 3);
+      fwd_finish<R, RKS>(A, ib * 64 + lane, ib * 64 + lane < A.n, ib, lane, v, h, h + 3);
     }
   } else {
     block_combine_store<Acc, NC, W>(red, o, w, lane, static_cast<Acc*>(A.partial), s, ib, A.n);
@@ -525,7 +537,7 @@ __device__ __forceinline__ void adj_block(const AdjArgs& A, int ib, int s,
     if (w == 0) {
       double h[NC];
       for (int c = 0; c < NC; ++c) h[c] = red[c * 64 + lane];
-      adj_finish<R, RKS>(A, ib, lane, v, h);
+      adj_finish9<R, RKS>(A, ib, lane, v, h);
     }
   } else {
     block_combine_store<Acc, NC, W>(red, o, w, lane, static_cast<Acc*>(A.partial), s, ib, A.n);
@@ -544,6 +556,257 @@ template <typename R, bool COMP, bool RKS, int W, int D>
 __global__ __launch_bounds__(64 * W) void k_adj(AdjArgs A) {
   __shared__ typename AccOf<R, COMP>::type red[W * 9 * 64];
   adj_block<R, COMP, RKS, W, D>(A, blockIdx.x / A.S, blockIdx.x % A.S, red);
+}
+
+// ---------------------------------------------------------------------------
+// row kernels: one launch per step
+// ---------------------------------------------------------------------------
+// Below a few thousand landmarks a step of the split kernels is two dependent
+// launches of 3 to 4 us whose pair sums take 1 to 3 us.  Here a workgroup holds
+// every j of its rows and ends the step itself.  The roles of the split
+// kernels' operands are swapped: lane l of a wave owns landmark j = 64 t + l of
+// tile t (loaded once per tile, coalesced, no LDS staging) and M landmarks i are
+// wave-uniform, so a workgroup can be as small as M rows and the chip fills from
+// n = 256 M on.  Each lane's M x 2D sums are added across the wave at the end:
+// two half-exchanges leave a quarter of the values per lane, the rest of the
+// sum (16 lanes x waves) is FP64 in every mode.  With T_w = n / (64 jg) <= 10
+// terms per lane the FP32 sums are short enough to need no tiles; both FP32
+// modes run the same code.
+// The adjoint is written on w = a_j + e p_j: pi + s e = a_i.p_j + p_i.w and B's
+// term is g w, and A1 / kappa and -A2 share one accumulator (p_j / kappa is formed
+// once per tile): 35 VALU + 1 exp per pair and 6 sums per row instead of 37 + 1
+// and 9.
+// What bounds them: at n = 1000 a step takes 4.7 us, of which 3.6 are a
+// dependent launch that loads, combines and stores (n = 64 takes as long); at n =
+// 4096 the loops (12.4 and 17.9 us per step against 10.2 and 16.3 at the rate of
+// the 65536-landmark kernels).
+template <typename R>
+using Vec3 = R __attribute__((ext_vector_type(3)));
+
+// 2^(-x) with an s_nop behind the transcendental.  FP32 instructions of two waves
+// issue together on a SIMD, but after a v_exp_f32 with only vector
+// instructions around it they stop doing so for some 20 cycles (issue probe, one
+// v_exp_f32 per 15 v_fmac_f32: 4.1 cycles per instruction, 2.8 with the s_nop);
+// it took 8 to 15 % off these loops.  The s_nop also covers the wait state
+// between a transcendental and its use.
+__device__ __forceinline__ float ex2n(float x) {
+  float g;
+  asm("v_exp_f32 %0, -%1\n\ts_nop 0" : "=v"(g) : "v"(x));
+  return g;
+}
+__device__ __forceinline__ double ex2n(double x) { return ex2(-x); }
+
+// Half-wave exchanges: a + b of the two halves, the low half of the result
+// holding a's sums and the high half b's (rows of 16 likewise in swap16_add).
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const unsigned al = __double2loint(a), ah = __double2hiint(a);
+  const unsigned bl = __double2loint(b), bh = __double2hiint(b);
+  const auto l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const unsigned al = __double2loint(a), ah = __double2hiint(a);
+  const unsigned bl = __double2loint(b), bh = __double2hiint(b);
+  const auto l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+  return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+}
+
+// v plus v of the lane CTRL (a row_ror) away within its row of 16.
+template <int CTRL>
+__device__ __forceinline__ double row_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return v + __hiloint2double(hi, lo);
+}
+
+template <typename R>
+constexpr int kRowWaves = std::is_same<R, double>::value ? 8 : 16;   // waves of a row workgroup at most
+
+// A wave-uniform value held in a vector register: the FP64 adjoint's rows do not
+// fit the scalar registers beside the exponential's constants (spilled, its
+// loops took 20 % longer).
+__device__ __forceinline__ double in_vgpr(double s) {
+  int lo, hi;
+  asm("v_mov_b32 %0, %1" : "=v"(lo) : "s"(__double2loint(s)));
+  asm("v_mov_b32 %0, %1" : "=v"(hi) : "s"(__double2hiint(s)));
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ float in_vgpr(float s) { return s; }
+constexpr int kRowGroups = 8;   // i-groups of a row workgroup at most
+
+// Sums of M rows, padded to a multiple of four (the combine halves them twice),
+// and where row k of a workgroup starts in its combined sums.
+template <int D, int M>
+constexpr int row_pad = (M * 2 * D + 3) / 4 * 4;
+template <int D, int M>
+__device__ __forceinline__ int row_at(int k) {
+  return (k / M) * row_pad<D, M> + (k % M) * 2 * D;
+}
+
+// Sums of one wave: rows i0 .. i0 + M - 1 over the tiles t = jg, jg + JG, ...
+// ADJ: h[m] = {A1 / kappa - A2 (D components), B (D)}, else {Hp (D), Hq's sums (D)}.
+template <typename R, bool ADJ, int D, int M>
+__device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, int i0, int jg,
+                                         int JG, int lane, R inv_kappa, R h[row_pad<D, M>]) {
+  const GlobalPtr<Rec<R>> X = global_ptr(static_cast<const Rec<R>*>(Xv));
+  const GlobalPtr<Rec<R>> Y = global_ptr(static_cast<const Rec<R>*>(Yv));
+  R xi[M][6], yi[M][6];
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int i = min(i0 + m, n - 1);
+    const Rec<R> a = load_rec<R>(X, i);
+    xi[m][0] = a.x; xi[m][1] = a.y; xi[m][2] = a.z;
+    xi[m][3] = a.px; xi[m][4] = a.py; xi[m][5] = a.pz;
+    if constexpr (ADJ) {
+      const Rec<R> b = load_rec<R>(Y, i);
+      yi[m][0] = in_vgpr(b.x); yi[m][1] = in_vgpr(b.y); yi[m][2] = in_vgpr(b.z);
+      yi[m][3] = in_vgpr(b.px); yi[m][4] = in_vgpr(b.py); yi[m][5] = in_vgpr(b.pz);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < row_pad<D, M>; ++k) h[k] = (R)0;
+  const int nt = (n + 63) >> 6;
+  for (int t = jg; t < nt; t += JG) {
+    const bool in = t * 64 + lane < n;
+    const int j = in ? t * 64 + lane : n - 1;
+    const Vec3<R>* xp = reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Xv)[j].x);
+    const Vec3<R>* pp = reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Xv)[j].px);
+    Vec3<R> q = *xp, p = *pp, a = (R)0, b = (R)0;
+    if constexpr (ADJ) {
+      a = *reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Yv)[j].x);
+      b = *reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Yv)[j].px);
+    }
+    if (!in) { q = (R)0; p = (R)0; a = (R)0; b = (R)0; }   // adds an exact 0 to every sum
+    Vec3<R> ps = p;
+    if constexpr (ADJ) ps = p * inv_kappa;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      R d[3];
+      R r2 = (R)0;
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        d[c] = xi[m][c] - q[c];
+        r2 = c == 0 ? d[c] * d[c] : fma(d[c], d[c], r2);
+      }
+      const R g = ex2n(r2);
+      R s = xi[m][3] * ps[0];
+#pragma unroll
+      for (int c = 1; c < D; ++c) s = fma(xi[m][3 + c], ps[c], s);
+      const R gs = g * s;
+      if constexpr (!ADJ) {
+#pragma unroll
+        for (int c = 0; c < D; ++c) h[2 * D * m + c] = fma(g, p[c], h[2 * D * m + c]);
+#pragma unroll
+        for (int c = 0; c < D; ++c) h[2 * D * m + D + c] = fma(gs, d[c], h[2 * D * m + D + c]);
+      } else {
+        R ex[3], w[3];
+        R e = (R)0, v = (R)0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+          ex[c] = yi[m][3 + c] - b[c];
+          e = c == 0 ? d[c] * ex[c] : fma(d[c], ex[c], e);
+        }
+#pragma unroll
+        for (int c = 0; c < D; ++c) w[c] = fma(e, p[c], a[c]);
+#pragma unroll
+        for (int c = 0; c < D; ++c) v = c == 0 ? yi[m][c] * p[c] : fma(yi[m][c], p[c], v);
+#pragma unroll
+        for (int c = 0; c < D; ++c) v = fma(xi[m][3 + c], w[c], v);
+        const R gv = g * v;
+#pragma unroll
+        for (int c = 0; c < D; ++c) h[2 * D * m + c] = fma(gs, ex[c], h[2 * D * m + c]);
+#pragma unroll
+        for (int c = 0; c < D; ++c) h[2 * D * m + c] = fma(-gv, d[c], h[2 * D * m + c]);
+#pragma unroll
+        for (int c = 0; c < D; ++c) h[2 * D * m + D + c] = fma(g, w[c], h[2 * D * m + D + c]);
+      }
+    }
+  }
+}
+
+// The workgroup's sums of rows [0, kRows ig) in fin[row][2 D], from every wave's h.
+template <typename R, int D, int M>
+__device__ __forceinline__ void row_combine(R h[row_pad<D, M>], R* red, double* fin, int ig, int jg,
+                                            int w, int lane) {
+  constexpr int NV = row_pad<D, M>, Q = NV / 4;
+  R* f = h;
+#pragma unroll
+  for (int k = 0; k < NV / 2; ++k) f[k] = swap32_add(f[k], f[k + NV / 2]);
+#pragma unroll
+  for (int k = 0; k < Q; ++k) f[k] = swap16_add(f[k], f[k + Q]);
+  // lanes 16 g .. 16 g + 15 now hold value k + Q g of the wave in f[k]
+#pragma unroll
+  for (int k = 0; k < Q; ++k) red[(w * Q + k) * 64 + lane] = f[k];
+  __syncthreads();
+  for (int kk = w; kk < Q * ig; kk += ig * jg) {
+    const int k = kk % Q, g = kk / Q;
+    double s = (double)red[(g * Q + k) * 64 + lane];
+    for (int v = 1; v < jg; ++v) s += (double)red[((v * ig + g) * Q + k) * 64 + lane];
+    s = row_add<0x121>(s);
+    s = row_add<0x122>(s);
+    s = row_add<0x124>(s);
+    s = row_add<0x128>(s);
+    if ((lane & 15) == 0) fin[g * NV + k + Q * (lane >> 4)] = s;
+  }
+  __syncthreads();
+}
+
+template <typename R, bool RKS, int D, int M>
+__global__ __launch_bounds__(64 * kRowWaves<R>) void k_fwd_rows(FwdArgs A) {
+  __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
+  __shared__ double fin[kRowGroups * row_pad<D, M>];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int row0 = blockIdx.x * A.ig * M;
+  R h[row_pad<D, M>];
+  FwdState v{};
+  if (w == 0) v = load_fwd_state<RKS>(A, row0 + lane);   // its latency under the sums
+  row_sums<R, false, D, M>(A.rec_t, nullptr, A.n, row0 + (w % A.ig) * M, w / A.ig, A.jg, lane,
+                        (R)0, h);
+  row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane);
+  if (w == 0) {
+    const bool own = lane < A.ig * M && row0 + lane < A.n;
+    double hp[3] = {0.0, 0.0, 0.0}, hq[3] = {0.0, 0.0, 0.0};
+    if (own)
+      for (int c = 0; c < D; ++c) {
+        hp[c] = fin[row_at<D, M>(lane) + c];
+        hq[c] = fin[row_at<D, M>(lane) + D + c];
+      }
+    fwd_finish<R, RKS>(A, row0 + lane, own, blockIdx.x, lane, v, hp, hq);
+  }
+}
+
+template <typename R, bool RKS, int D, int M>
+__global__ __launch_bounds__(64 * kRowWaves<R>) void k_adj_rows(AdjArgs A) {
+  __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
+  __shared__ double fin[kRowGroups * row_pad<D, M>];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int row0 = blockIdx.x * A.ig * M;
+  R h[row_pad<D, M>];
+  AdjState v{};
+  if (w == 0) v = load_adj_state<RKS>(A, row0 + lane);   // its latency under the sums
+  row_sums<R, true, D, M>(A.rec_t, A.arec, A.n, row0 + (w % A.ig) * M, w / A.ig, A.jg, lane,
+                       (R)(1.0 / A.sc.kappa), h);
+  row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane);
+  if (w == 0 && lane < A.ig * M && row0 + lane < A.n) {
+    double sa[3] = {0.0, 0.0, 0.0}, sb[3] = {0.0, 0.0, 0.0};
+    for (int c = 0; c < D; ++c) {
+      sa[c] = fin[row_at<D, M>(lane) + c];
+      sb[c] = fin[row_at<D, M>(lane) + D + c];
+    }
+    adj_finish<R, RKS>(A, row0 + lane, v, sa, sb);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -736,7 +999,7 @@ __global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_fwd_update(FwdArgs A
   double h[6];
   gather_partials<Acc, 6, SC>(static_cast<const Acc*>(A.partial), A.n, A.S,
                               min(ib * 64 + lane, A.n - 1), h);
-  fwd_finish<R, RKS>(A, ib, lane, v, h, h + 3);
+  fwd_finish<R, RKS>(A, ib * 64 + lane, ib * 64 + lane < A.n, ib, lane, v, h, h + 3);
 }
 
 template <typename R, bool COMP, int SC, bool RKS>
@@ -747,7 +1010,7 @@ __global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_adj_update(AdjArgs A
   double h[9];
   gather_partials<Acc, 9, SC>(static_cast<const Acc*>(A.partial), A.n, A.S,
                               min(ib * 64 + lane, A.n - 1), h);
-  adj_finish<R, RKS>(A, ib, lane, v, h);
+  adj_finish9<R, RKS>(A, ib, lane, v, h);
 }
 
 // The same with two waves per i-block, for SC >= 8: one lane's 9 SC partial
@@ -775,7 +1038,7 @@ __global__ __launch_bounds__(128) LDDMM_LATENCY_BOUND void k_adj_update2(AdjArgs
   __syncthreads();
   if (w == 0) {
     for (int c = 5; c < 9; ++c) h[c] = red[(c - 5) * 64 + lane];
-    adj_finish<R, RKS>(A, ib, lane, v, h);
+    adj_finish9<R, RKS>(A, ib, lane, v, h);
   }
 }
 
@@ -1109,6 +1372,58 @@ hipError_t adj_dispatch(const Plan& p, const AdjArgs& a, hipStream_t s, hipEvent
   return hipGetLastError();
 }
 
+// Row kernels (RowPlan): the whole step in one launch.
+template <typename R, bool RKS, int M>
+hipError_t fwd_rows_launch(const RowPlan& p, const FwdArgs& a, hipStream_t s, hipEvent_t* ev) {
+  launch_timed(a.dim == 2 ? k_fwd_rows<R, RKS, 2, M> : k_fwd_rows<R, RKS, 3, M>,
+               dim3((unsigned)p.groups), 64u * (unsigned)(p.ig * p.jg), s, a, ev);
+  return hipGetLastError();
+}
+template <typename R, bool RKS, int M>
+hipError_t adj_rows_launch(const RowPlan& p, const AdjArgs& a, hipStream_t s, hipEvent_t* ev) {
+  launch_timed(a.dim == 2 ? k_adj_rows<R, RKS, 2, M> : k_adj_rows<R, RKS, 3, M>,
+               dim3((unsigned)p.groups), 64u * (unsigned)(p.ig * p.jg), s, a, ev);
+  return hipGetLastError();
+}
+
+template <bool RKS>
+hipError_t fwd_rows_dispatch(int mode, const RowPlan& p, const FwdArgs& a, hipStream_t s,
+                             hipEvent_t* ev) {
+  if (mode == kFP64) {
+    switch (p.m) {
+      case 2: return fwd_rows_launch<double, RKS, 2>(p, a, s, ev);
+      case 3: return fwd_rows_launch<double, RKS, 3>(p, a, s, ev);
+      case 4: return fwd_rows_launch<double, RKS, 4>(p, a, s, ev);
+    }
+  } else {
+    switch (p.m) {
+      case 3: return fwd_rows_launch<float, RKS, 3>(p, a, s, ev);
+      case 4: return fwd_rows_launch<float, RKS, 4>(p, a, s, ev);
+      case 5: return fwd_rows_launch<float, RKS, 5>(p, a, s, ev);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+template <bool RKS>
+hipError_t adj_rows_dispatch(int mode, const RowPlan& p, const AdjArgs& a, hipStream_t s,
+                             hipEvent_t* ev) {
+  if (mode == kFP64) {
+    switch (p.m) {
+      case 2: return adj_rows_launch<double, RKS, 2>(p, a, s, ev);
+      case 3: return adj_rows_launch<double, RKS, 3>(p, a, s, ev);
+      case 4: return adj_rows_launch<double, RKS, 4>(p, a, s, ev);
+    }
+  } else {
+    switch (p.m) {
+      case 3: return adj_rows_launch<float, RKS, 3>(p, a, s, ev);
+      case 4: return adj_rows_launch<float, RKS, 4>(p, a, s, ev);
+      case 5: return adj_rows_launch<float, RKS, 5>(p, a, s, ev);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
 inline unsigned blocks256(int n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
@@ -1148,6 +1463,11 @@ hipError_t launch_restore(int mode, int n, const double* ckpt, double k, double*
 hipError_t launch_fwd_step(int mode, const Plan& p, const FwdArgs& a, hipStream_t s,
                            hipEvent_t* ev) {
   const bool rk = a.rk != 0;
+  if (p.row.m > 0) {
+    if (mode != kFP32 && mode != kFP32Comp && mode != kFP64) return hipErrorInvalidValue;
+    return rk ? fwd_rows_dispatch<true>(mode, p.row, a, s, ev)
+              : fwd_rows_dispatch<false>(mode, p.row, a, s, ev);
+  }
   switch (mode) {
     case kFP32:
       return rk ? fwd_dispatch<float, false, true>(p, a, s, ev)
@@ -1165,6 +1485,11 @@ hipError_t launch_fwd_step(int mode, const Plan& p, const FwdArgs& a, hipStream_
 hipError_t launch_adj_step(int mode, const Plan& p, const AdjArgs& a, hipStream_t s,
                            hipEvent_t* ev) {
   const bool rk = a.rk != 0;
+  if (p.row.m > 0) {
+    if (mode != kFP32 && mode != kFP32Comp && mode != kFP64) return hipErrorInvalidValue;
+    return rk ? adj_rows_dispatch<true>(mode, p.row, a, s, ev)
+              : adj_rows_dispatch<false>(mode, p.row, a, s, ev);
+  }
   switch (mode) {
     case kFP32:
       return rk ? adj_dispatch<float, false, true>(p, a, s, ev)
