@@ -350,9 +350,8 @@ lddmm_status run_grad(lddmm_ctx* ctx, const Job& j, const double* q0, const doub
   if (!tm) tm = &ctx->timer;
   const lddmm_params* params = &j.p;
   const int n = params->n, T = params->T, mode = params->precision;
-  HIP_TRY(ctx, launch_centroid(q0, n, j.cen, s), "centroid");
-  HIP_TRY(ctx, launch_stage(mode, n, q0, p0, target, j.cen, j.sc.k, j.st, j.xc, j.rec(0), s),
-          "stage");
+  HIP_TRY(ctx, launch_stage(mode, n, q0, p0, target, j.cen, j.ad, j.sc.k, j.st, j.xc, j.rec(0),
+                            s), "stage");
   if (j.L.nseg > 0)
     HIP_TRY(ctx, hipMemcpyAsync(j.ckpt_state(0), j.st, 6 * (size_t)n * 8, hipMemcpyDeviceToDevice, s),
             "checkpoint 0");
@@ -482,9 +481,8 @@ lddmm_status lddmm_shoot_forward(lddmm_ctx* ctx, const lddmm_params* params, con
   if (st != LDDMM_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n = params->n;
-  HIP_TRY(ctx, launch_centroid(q0, n, j.cen, s), "centroid");
-  HIP_TRY(ctx, launch_stage(params->precision, n, q0, p0, nullptr, j.cen, j.sc.k, j.st, j.xc,
-                            j.rec(0), s), "stage");
+  HIP_TRY(ctx, launch_stage(params->precision, n, q0, p0, nullptr, j.cen, j.ad, j.sc.k, j.st,
+                            j.xc, j.rec(0), s), "stage");
   HIP_TRY(ctx, run_forward(j, 0, params->T, true, false, s, &ctx->timer), "forward step");
   HIP_TRY(ctx, launch_forward_out(n, j.nh, j.st, j.cen, j.h0p, H0, q1, p1, s), "forward out");
   return LDDMM_OK;
@@ -538,13 +536,13 @@ lddmm_status lddmm_shoot_grad_all(lddmm_ctx* ctx, const lddmm_params* params, co
 
 namespace {
 
-FlowArgs flow_args(const Job& j, int m, int W) {
+FlowArgs flow_args(const Job& j, int m) {
   FlowArgs a{};
   a.n = j.p.n;
   a.m = m;
   a.slots = j.L.slots;
   a.spt = j.spt;
-  a.wchunk = (j.p.n + W - 1) / W;
+  flow_chunks(a);
   a.dim = j.dim;
   a.k = j.sc.k;
   a.dt = j.sc.dt;
@@ -573,16 +571,17 @@ lddmm_status lddmm_velocity(lddmm_ctx* ctx, const lddmm_params* params, const do
   if (m == 0) return LDDMM_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n = one.n;
-  HIP_TRY(ctx, launch_centroid(q, n, j.cen, s), "centroid");
-  HIP_TRY(ctx, launch_stage(one.precision, n, q, p, nullptr, j.cen, j.sc.k, j.st, j.xc, j.rec(0), s),
-          "stage");
-  const int W = flow_waves(n);
-  FlowArgs a = flow_args(j, m, W);
+  HIP_TRY(ctx, launch_stage(one.precision, n, q, p, nullptr, j.cen, j.ad, j.sc.k, j.st, j.xc,
+                            j.rec(0), s), "stage");
+  FlowArgs a = flow_args(j, m);
   a.t0 = 0;
   a.t1 = 1;
   a.x_in = x;
   a.v_out = v;
-  HIP_TRY(ctx, launch_flow(one.precision, W, a, s, ctx->timer.take(2)), "velocity");
+  // the pair sums' partials are free here
+  if ((size_t)a.pairs * 3 * (size_t)m * 8 <= j.L.hpT - j.L.partial)
+    a.v_part = static_cast<double*>(j.partial);
+  HIP_TRY(ctx, launch_flow(one.precision, a, s, ctx->timer.take(2)), "velocity");
   return LDDMM_OK;
 }
 
@@ -600,10 +599,8 @@ lddmm_status lddmm_flow(lddmm_ctx* ctx, const lddmm_params* params, const double
   if (st != LDDMM_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n = params->n, T = params->T;
-  HIP_TRY(ctx, launch_centroid(q0, n, j.cen, s), "centroid");
-  HIP_TRY(ctx, launch_stage(params->precision, n, q0, p0, nullptr, j.cen, j.sc.k, j.st, j.xc,
-                            j.rec(0), s), "stage");
-  const int W = flow_waves(n);
+  HIP_TRY(ctx, launch_stage(params->precision, n, q0, p0, nullptr, j.cen, j.ad, j.sc.k, j.st,
+                            j.xc, j.rec(0), s), "stage");
   double* xs = at<double>(ctx->ws, j.L.total);
   // Segments of the landmark forward pass, each followed by the points' steps
   // over the same records (one segment when the whole trajectory is kept).
@@ -612,13 +609,13 @@ lddmm_status lddmm_flow(lddmm_ctx* ctx, const lddmm_params* params, const double
     const int t1 = t0 + every < T ? t0 + every : T;
     HIP_TRY(ctx, run_forward(j, t0, t1, t0 == 0, false, s, &ctx->timer), "forward step");
     if (m == 0) continue;
-    FlowArgs a = flow_args(j, m, W);
+    FlowArgs a = flow_args(j, m);
     a.t0 = t0;
     a.t1 = t1;
     a.x_in = t0 == 0 ? x0 : nullptr;
     a.x_out = t1 == T ? x1 : nullptr;
     a.xs = xs;
-    HIP_TRY(ctx, launch_flow(params->precision, W, a, s, ctx->timer.take(2)), "point flow");
+    HIP_TRY(ctx, launch_flow(params->precision, a, s, ctx->timer.take(2)), "point flow");
   }
   if (q1 || p1)
     HIP_TRY(ctx, launch_forward_out(n, j.nh, j.st, j.cen, j.h0p, nullptr, q1, p1, s),

@@ -267,9 +267,8 @@ bool admit(lddmm_server* s, ServerJob* j, int k) {
     p_in = B.gt;   // scratch until the first evaluation writes it
     W_TRY(s, hipMemcpyAsync(p_in, j->p0in.data(), m3 * 8, hipMemcpyHostToDevice, st), "p0 copy");
   }
-  W_TRY(s, launch_centroid(q0, n, b.cen, st), "centroid");
   // centred target (the state and record it also writes are rewritten every round)
-  W_TRY(s, launch_stage(mode, n, q0, q0, x, b.cen, sc.k, b.st, b.xc, b.traj, st), "stage");
+  W_TRY(s, launch_stage(mode, n, q0, q0, x, b.cen, b.ad, sc.k, b.st, b.xc, b.traj, st), "stage");
   W_TRY(s, launch_lbfgs_init(B, lj.state, j->o.init, q0, x, p_in, T, st), "solver init");
   s->tab[k] = b;
   s->ltab[k] = lj;

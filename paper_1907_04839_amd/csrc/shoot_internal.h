@@ -62,9 +62,10 @@ struct AdjArgs {
 constexpr size_t kScratchBytes = size_t(64) << 20;
 hipError_t scratch_address(int device, void** out);
 
-hipError_t launch_centroid(const double* q0, int n, double* cen, hipStream_t s);
+// Centroid of q0 (written to cen) and the FP64 state, centred target (x may be
+// null) and first records.  part: scratch of 3 doubles per 4096 landmarks.
 hipError_t launch_stage(int mode, int n, const double* q0, const double* p0, const double* x,
-                        const double* cen, double k, double* st, double* xc, void* rec0,
+                        double* cen, double* part, double k, double* st, double* xc, void* rec0,
                         hipStream_t s);
 hipError_t launch_restore(int mode, int n, const double* ckpt, double k, double* st, void* rec,
                           hipStream_t s);
@@ -75,15 +76,18 @@ hipError_t launch_adj_step(int mode, const Plan& p, const AdjArgs& a, hipStream_
                            hipEvent_t* ev = nullptr);
 // Points carried by the landmark motion (eq. 4): over steps [t0, t1) of a
 // stored trajectory, x <- x + dt v(x, t) with v(x, t) = sum_l g(|q_l(t) - x|)
-// p_l(t).  One lane owns one point for all the steps; the landmarks are split
-// over the W waves of a workgroup and combined in wave order every step.
+// p_l(t).  The landmarks are cut into `pairs` pairs of chunks, by their number
+// alone, and a point's velocity is the sum over the pairs in order of (first
+// chunk + second chunk): its result depends neither on the other points nor on
+// the launch that their number selects.
 struct FlowArgs {
   int n, m;             // landmarks, points
   int t0, t1;           // steps
   int slots;            // trajectory slots: record r is slot r % slots
   int spt;              // records per step: 1 (Euler), 4 (Runge-Kutta stage states;
                         // record spt t + s is stage s + 1 of step t)
-  int wchunk;           // landmarks per wave
+  int pairs, clen;      // chunk pairs, landmarks per chunk (a multiple of 64)
+  int half;             // a wave sums one chunk (else a pair of them)
   int dim;              // 3, or 2 for planar problems
   double k, dt;
   const void* traj;     // landmark records (k q, p), slot-major
@@ -92,14 +96,14 @@ struct FlowArgs {
   double* xs;           // [3][m] centred FP64 point state between segments
   double* x_out;        // [m][3] uncentred points after t1 (last segment), else write xs
   double* v_out;        // [m][3]: write v(x, t0) and take no step (t1 == t0 + 1)
+  double* v_part;       // [pairs][3][m], with v_out and split: the pairs' velocities
 };
 
-// Waves per workgroup of the flow kernel for n landmarks (1, 2, 4, 8 or 16;
-// LDDMM_FLOW_WAVES overrides it).  It depends on n only, so a point's result
-// does not depend on how many other points are carried with it.
-int flow_waves(int n);
-hipError_t launch_flow(int mode, int W, const FlowArgs& a, hipStream_t s,
-                       hipEvent_t* ev = nullptr);
+// Fills a's chunks for its n.
+void flow_chunks(FlowArgs& a);
+// With a.v_out and v_part room for [pairs][3][m] doubles, the pairs of a launch
+// too small for the chip are spread over workgroups and summed by a second one.
+hipError_t launch_flow(int mode, const FlowArgs& a, hipStream_t s, hipEvent_t* ev = nullptr);
 
 // Loss and terminal adjoint: L = E + lambda |q(1) - x|^2, a = 2 lambda (q(1) - x), b = 0,
 // with the energy term E summed from h0_part.  With hqT/hpT ([3][n], the forward sums at the

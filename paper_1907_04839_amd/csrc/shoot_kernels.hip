@@ -812,102 +812,241 @@ __global__ __launch_bounds__(64 * kRowWaves<R>) void k_adj_rows(AdjArgs A) {
 // ---------------------------------------------------------------------------
 // flow of arbitrary points (eq. 4)
 // ---------------------------------------------------------------------------
-// v += sum_j g(x, q_j) p_j over landmarks j in [j0, j1) for the lane's point
-// (pre-scaled coordinates xs = k x): 9 VALU + 1 exp per pair.
-template <typename R, int D>
-__device__ __forceinline__ void vel_range(const Rec<R>* __restrict__ Xp, R x0, R x1, R x2,
-                                          int j0, int j1, R h[3]) {
-  const GlobalPtr<Rec<R>> X = global_ptr(Xp);
-  R v0 = h[0], v1 = h[1], v2 = h[2];
-#pragma unroll 4
-  for (int j = j0; j < j1; ++j) {
-    const Rec<R> rj = load_rec<R>(X, j);
-    const R dx = x0 - rj.x, dy = x1 - rj.y;
-    R r2 = dx * dx;
-    r2 = fma(dy, dy, r2);
-    if constexpr (D == 3) {
-      const R dz = x2 - rj.z;
-      r2 = fma(dz, dz, r2);
-    }
-    const R g = ex2(-r2);
-    v0 = fma(g, rj.px, v0);
-    v1 = fma(g, rj.py, v1);
-    if constexpr (D == 3) v2 = fma(g, rj.pz, v2);
+// Lane l owns RP points.  With FP32 sums a wave copies its landmarks to its own
+// LDS tile, 64 at a time, and reads them back as broadcasts, so that every
+// operand of a pair is a vector register: an FP32 instruction with a scalar
+// operand issues beside one without, not beside another with, and with the
+// landmark in scalar registers 6 of the pair's 9 have one.  9 VALU + 1 exp per
+// pair; two points per lane halve the LDS reads per pair (25 cycles of a SIMD's
+// share of the LDS with one, against 37 of issue).  What bounds it is issue: on
+// the 64^3 grid around 4096 landmarks a step takes 242 us, 35 cycles per pair and
+// wave, against 30 if every instruction found a partner and 40 (276 us) with
+// scalar operands.
+constexpr int kFlowTile = 64;
+
+template <int D>
+struct FlowTile;
+template <>
+struct alignas(16) FlowTile<3> {
+  float4 a[kFlowTile];
+  float2 b[kFlowTile];
+  __device__ void put(int l, const Rec<float>& r) {
+    a[l] = make_float4(r.x, r.y, r.z, r.px);
+    b[l] = make_float2(r.py, r.pz);
   }
-  h[0] = v0; h[1] = v1; h[2] = v2;
+  __device__ void get(int j, float q[3], float p[3]) const {
+    const float4 u = a[j];
+    const float2 v = b[j];
+    q[0] = u.x; q[1] = u.y; q[2] = u.z; p[0] = u.w; p[1] = v.x; p[2] = v.y;
+  }
+};
+template <>
+struct alignas(16) FlowTile<2> {
+  float4 a[kFlowTile];
+  __device__ void put(int l, const Rec<float>& r) { a[l] = make_float4(r.x, r.y, r.px, r.py); }
+  __device__ void get(int j, float q[3], float p[3]) const {
+    const float4 u = a[j];
+    q[0] = u.x; q[1] = u.y; p[0] = u.z; p[1] = u.w;
+  }
+};
+// A wave's LDS: its tile, and over it (between the sums) its sums for the combine.
+template <int RP>
+constexpr int kFlowWaveLds = RP * 3 * 64 * 8;
+static_assert(sizeof(FlowTile<3>) <= kFlowWaveLds<1>, "a tile fits its wave's sums");
+
+// o += sum over landmarks [c0, c1) of g(x, q_j) p_j for the lane's pre-scaled
+// points xs.  FP32: tiles of 64 terms through the wave's LDS, each folded into FP64.
+template <int D, int RP>
+__device__ __forceinline__ void flow_chunk(const Rec<float>* __restrict__ X, void* lds,
+                                           const float xs[RP][3], int c0, int c1, int lane,
+                                           double o[RP][3]) {
+  FlowTile<D>& tile = *static_cast<FlowTile<D>*>(lds);
+  for (int s = c0; s < c1; s += kFlowTile) {
+    Rec<float> rec = X[min(s + lane, c1 - 1)];
+    if (s + lane >= c1) { rec.px = 0.0f; rec.py = 0.0f; rec.pz = 0.0f; }
+    tile.put(lane, rec);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    float v[RP][3];
+#pragma unroll
+    for (int r = 0; r < RP; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[r][c] = 0.0f;
+#pragma unroll 2
+    for (int j = 0; j < kFlowTile; ++j) {
+      float q[3], p[3];
+      tile.get(j, q, p);
+#pragma unroll
+      for (int r = 0; r < RP; ++r) {
+        float r2 = 0.0f;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+          const float d = xs[r][c] - q[c];
+          r2 = c == 0 ? d * d : fma(d, d, r2);
+        }
+        const float g = ex2n(r2);
+#pragma unroll
+        for (int c = 0; c < D; ++c) v[r][c] = fma(g, p[c], v[r][c]);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RP; ++r)
+#pragma unroll
+      for (int c = 0; c < D; ++c) o[r][c] += (double)v[r][c];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
 }
 
-// One workgroup: 64 points (one per lane) through all steps [t0, t1).  Every
-// wave keeps the same FP64 copy of its lanes' points; wave w sums landmarks
-// [w wchunk, (w+1) wchunk) and the W sums are combined in wave order, so the
-// result depends on n and W only.
-template <typename R, bool COMP, bool RKS, int W, int D>
-__global__ __launch_bounds__(64 * W) void k_flow(FlowArgs A) {
-  using Acc = typename AccOf<R, COMP>::type;
-  __shared__ Acc red[W > 1 ? W * 3 * 64 : 1];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int i = blockIdx.x * 64 + lane;
-  const int ic = min(i, A.m - 1);
-  double x[3];
-  for (int c = 0; c < 3; ++c)
-    x[c] = A.x_in ? A.x_in[3 * (size_t)ic + c] - A.cen[c] : A.xs[(size_t)c * A.m + ic];
-  const int j0 = min(A.n, w * A.wchunk);
-  const int j1 = min(A.n, j0 + A.wchunk);
-  double v[3] = {0.0, 0.0, 0.0};
-  // Runge-Kutta steps: v = velocity at the position y from stage record r
-  auto velocity = [&](int r, const double y[3]) {
-    const Rec<R>* X = static_cast<const Rec<R>*>(A.traj) + (size_t)(r % A.slots) * A.n;
-    const R s0 = (R)(A.k * y[0]), s1 = (R)(A.k * y[1]), s2 = (R)(A.k * y[2]);
-    Acc o[3];
-    wave_sums<R, COMP, 3>(j0, j1, o,
-                          [&](int a, int b, auto* h) { vel_range<R, D>(X, s0, s1, s2, a, b, h); });
-    if constexpr (W > 1) {
-      block_combine<Acc, 3, W>(red, o, w, lane);
-      for (int c = 0; c < 3; ++c) v[c] = red[c * 64 + lane];
-      __syncthreads();   // red is rewritten by the next sum
-    } else {
-      for (int c = 0; c < 3; ++c) v[c] = o[c];
-    }
-  };
-  for (int t = A.t0; t < A.t1; ++t) {
-    if constexpr (RKS) {
-      // Runge-Kutta step of the point with the landmarks' stage states:
-      // stage positions x + c v_prev (c = 0, dt/2, dt/2, dt), then
-      // x + dt/6 (v1 + 2 v2 + 2 v3 + v4)
-      double acc[3], y[3];
-      for (int st = 0; st < 4; ++st) {
-        const double cs = st == 3 ? A.dt : 0.5 * A.dt;
-        for (int c = 0; c < 3; ++c) y[c] = st == 0 ? x[c] : x[c] + cs * v[c];
-        velocity(4 * t + st, y);
-        for (int c = 0; c < 3; ++c)
-          if (st < 3) acc[c] = st == 0 ? v[c] : acc[c] + 2.0 * v[c];
+// FP64: no co-issue to gain, so the landmarks come as scalar operands.  The
+// records do not change while the kernel runs, which the constant address space
+// states: behind the barriers and stores of the loop over the steps the compiler
+// would load them per lane otherwise (2.2 times slower).
+using ConstRec = const __attribute__((address_space(4))) Vec8<double>*;
+
+template <int D, int RP>
+__device__ __forceinline__ void flow_chunk(const Rec<double>* __restrict__ Xp, void*,
+                                           const double xs[RP][3], int c0, int c1, int,
+                                           double o[RP][3]) {
+  const ConstRec X = (ConstRec)(uintptr_t)Xp;
+#pragma unroll 4
+  for (int j = c0; j < c1; ++j) {
+    const Vec8<double> rj = X[j];
+    const double q[3] = {rj[0], rj[1], rj[2]}, p[3] = {rj[4], rj[5], rj[6]};
+#pragma unroll
+    for (int r = 0; r < RP; ++r) {
+      double r2 = 0.0;
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        const double d = xs[r][c] - q[c];
+        r2 = c == 0 ? d * d : fma(d, d, r2);
       }
-      for (int c = 0; c < 3; ++c) x[c] = x[c] + A.dt / 6.0 * (acc[c] + v[c]);
-    } else {
-      const Rec<R>* X = static_cast<const Rec<R>*>(A.traj) + (size_t)(t % A.slots) * A.n;
-      const R s0 = (R)(A.k * x[0]), s1 = (R)(A.k * x[1]), s2 = (R)(A.k * x[2]);
-      Acc o[3];
-      wave_sums<R, COMP, 3>(
-          j0, j1, o, [&](int a, int b, auto* h) { vel_range<R, D>(X, s0, s1, s2, a, b, h); });
-      if constexpr (W > 1) {
-        block_combine<Acc, 3, W>(red, o, w, lane);
-        for (int c = 0; c < 3; ++c) v[c] = red[c * 64 + lane];
-        __syncthreads();   // red is rewritten by the next step
-      } else {
-        for (int c = 0; c < 3; ++c) v[c] = o[c];
-      }
-      if (A.v_out) break;
-      for (int c = 0; c < 3; ++c) x[c] = x[c] + A.dt * v[c];
+      const double g = ex2(-r2);
+#pragma unroll
+      for (int c = 0; c < D; ++c) o[r][c] = fma(g, p[c], o[r][c]);
     }
   }
-  if (w != 0 || i >= A.m) return;
-  if (A.v_out) {
-    for (int c = 0; c < 3; ++c) A.v_out[3 * (size_t)i + c] = v[c];
-  } else if (A.x_out) {
-    for (int c = 0; c < 3; ++c) A.x_out[3 * (size_t)i + c] = x[c] + A.cen[c];
-  } else {
-    for (int c = 0; c < 3; ++c) A.xs[(size_t)c * A.m + i] = x[c];
+}
+
+// One workgroup: 64 RP points through all steps [t0, t1).  Wave w sums its chunk
+// (half) or pair of chunks; the sums are combined pair by pair in order.  Row k =
+// 3 r + c of the points' state (component c of point r of each lane) belongs to
+// wave k mod W, which combines and advances it; the positions go to the other
+// waves through LDS, so that no wave holds FP64 state through its sums.
+template <typename R, bool RKS, int D, int RP>
+__global__ __launch_bounds__(1024) void k_flow(FlowArgs A) {
+  extern __shared__ __align__(16) unsigned char flow_lds[];
+  __shared__ double xl[RP * 3][64];                   // positions
+  __shared__ R yl[RP * 3][64];                        // positions of the sums, pre-scaled
+  __shared__ double al[RKS ? RP * 3 : 1][64];         // k1 + 2 k2 + 2 k3
+  constexpr int kWave = kFlowWaveLds<RP>;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int W = blockDim.x >> 6;
+  const auto red = [&](int v) { return reinterpret_cast<double*>(flow_lds + v * kWave); };
+  const auto point = [&](int k) { return (int)(blockIdx.x * RP + k / 3) * 64 + lane; };
+  for (int k = w; k < RP * 3; k += W) {
+    const int c = k % 3, ic = min(point(k), A.m - 1);
+    const double x = A.x_in ? A.x_in[3 * (size_t)ic + c] - A.cen[c] : A.xs[(size_t)c * A.m + ic];
+    xl[k][lane] = x;
+    yl[k][lane] = (R)(A.k * x);
+  }
+  const bool split = gridDim.y > 1;   // the pairs are spread over workgroups
+  const int ch0 = A.half ? (int)blockIdx.y * W + w : 2 * w;
+  const int stages = RKS ? 4 : 1;
+  for (int t = stages * A.t0; t < stages * A.t1; ++t) {   // records: steps or their stages
+    __syncthreads();   // yl is written; the sums of the last record are read
+    const Rec<R>* X = static_cast<const Rec<R>*>(A.traj) + (size_t)(t % A.slots) * A.n;
+    R ys[RP][3];
+    double o[RP][3], o2[RP][3];
+#pragma unroll
+    for (int r = 0; r < RP; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        ys[r][c] = yl[3 * r + c][lane];
+        o[r][c] = o2[r][c] = 0.0;
+      }
+    const auto chunk = [&](int ch, double s[RP][3]) {
+      flow_chunk<D, RP>(X, red(w), ys, min(A.n, ch * A.clen), min(A.n, (ch + 1) * A.clen), lane, s);
+    };
+    chunk(ch0, o);
+    if (!A.half) chunk(ch0 + 1, o2);
+#pragma unroll
+    for (int r = 0; r < RP; ++r)
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        if (!A.half) o[r][c] += o2[r][c];
+        red(w)[(3 * r + c) * 64 + lane] = o[r][c];
+      }
+    __syncthreads();
+    if (split) break;
+    for (int k = w; k < RP * 3; k += W) {
+      double v = 0.0;
+      if (k % 3 < D) {
+        const int e = k * 64 + lane;
+        if (A.half) {
+          v = red(0)[e] + red(1)[e];
+          for (int u = 2; u < W; u += 2) v += red(u)[e] + red(u + 1)[e];
+        } else {
+          v = red(0)[e];
+          for (int u = 1; u < W; ++u) v += red(u)[e];
+        }
+      }
+      if (A.v_out) {   // one record: stored below
+        xl[k][lane] = v;
+        continue;
+      }
+      const double x = xl[k][lane];
+      double y;
+      if constexpr (RKS) {
+        // stage positions x + c v (c = dt/2, dt/2, dt), then x + dt/6 (v1 + 2 v2 + 2 v3 + v4)
+        const int st = t & 3;
+        const double acc = st == 0 ? 0.0 : al[k][lane];
+        if (st < 3) {
+          al[k][lane] = st == 0 ? v : acc + 2.0 * v;
+          y = x + (st == 2 ? A.dt : 0.5 * A.dt) * v;
+        } else {
+          y = x + A.dt / 6.0 * (acc + v);
+          xl[k][lane] = y;
+        }
+      } else {
+        y = x + A.dt * v;
+        xl[k][lane] = y;
+      }
+      yl[k][lane] = (R)(A.k * y);
+    }
+  }
+  if (split) {   // wave u writes the sum of the workgroup's pair u
+    if (w >= W / 2) return;
+    const int pair = (int)blockIdx.y * (W / 2) + w;
+    for (int r = 0; r < RP; ++r)
+      for (int c = 0; c < D; ++c) {
+        const int e = (3 * r + c) * 64 + lane;
+        if (point(3 * r) < A.m)
+          A.v_part[((size_t)pair * 3 + c) * A.m + point(3 * r)] = red(2 * w)[e] + red(2 * w + 1)[e];
+      }
+    return;
+  }
+  for (int k = w; k < RP * 3; k += W) {
+    const int c = k % 3, i = point(k);
+    if (i >= A.m) continue;
+    if (A.v_out) A.v_out[3 * (size_t)i + c] = xl[k][lane];
+    else if (A.x_out) A.x_out[3 * (size_t)i + c] = xl[k][lane] + A.cen[c];
+    else A.xs[(size_t)c * A.m + i] = xl[k][lane];
+  }
+}
+
+// v = sum over the pairs in order (planar: z is 0).
+__global__ __launch_bounds__(256) void k_flow_sum(int m, int pairs, int dim,
+                                                  const double* __restrict__ part,
+                                                  double* __restrict__ v) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= m) return;
+  for (int c = 0; c < 3; ++c) {
+    double s = 0.0;
+    if (c < dim) {
+      s = part[(size_t)c * m + i];
+      for (int u = 1; u < pairs; ++u) s += part[((size_t)u * 3 + c) * m + i];
+    }
+    v[3 * (size_t)i + c] = s;
   }
 }
 
@@ -943,15 +1082,27 @@ inline void launch_timed(void (*kernel)(A), dim3 grid, unsigned threads, hipStre
     default: return hipErrorInvalidValue;                                                    \
   }
 
-template <typename R, bool COMP>
-hipError_t flow_dispatch(int W, const FlowArgs& a, hipStream_t s, hipEvent_t* ev) {
-  const dim3 grid((unsigned)((a.m + 63) / 64));
-  if (a.spt == 4) {
-    LDDMM_LAUNCH_WD(W, a.dim, grid, s, a, ev, k_flow, R, COMP, true)
-  } else {
-    LDDMM_LAUNCH_WD(W, a.dim, grid, s, a, ev, k_flow, R, COMP, false)
-  }
+template <typename R, bool RKS, int D>
+hipError_t flow_run(const FlowArgs& a, dim3 grid, int W, int rp, hipStream_t s, hipEvent_t* ev) {
+  const unsigned lds = (unsigned)(W * (rp == 2 ? kFlowWaveLds<2> : kFlowWaveLds<1>));
+  auto kernel = k_flow<R, RKS, D, 1>;
+  if constexpr (std::is_same<R, float>::value)
+    if (rp == 2) kernel = k_flow<R, RKS, D, 2>;
+  if (ev)
+    hipExtLaunchKernelGGL(kernel, grid, dim3(64u * W), lds, s, ev[0], ev[1], 0, a);
+  else
+    kernel<<<grid, 64 * W, lds, s>>>(a);
   return hipGetLastError();
+}
+
+template <typename R>
+hipError_t flow_dispatch(const FlowArgs& a, dim3 grid, int W, int rp, hipStream_t s,
+                         hipEvent_t* ev) {
+  if (a.spt == 4)
+    return a.dim == 2 ? flow_run<R, true, 2>(a, grid, W, rp, s, ev)
+                      : flow_run<R, true, 3>(a, grid, W, rp, s, ev);
+  return a.dim == 2 ? flow_run<R, false, 2>(a, grid, W, rp, s, ev)
+                    : flow_run<R, false, 3>(a, grid, W, rp, s, ev);
 }
 
 // Split path (S > 1): combine the S workgroup partials in chunk order, then
@@ -1076,43 +1227,65 @@ __device__ __forceinline__ void block_sums(double v[K], double* red) {
   __syncthreads();
 }
 
-// Centroid of q0: per thread the points i = t, t + kLossThreads, ... in
-// increasing i (two points' loads in flight at a time), then one tree per
-// coordinate.
-__global__ __launch_bounds__(kLossThreads) void k_centroid(const double* __restrict__ q0, int n,
-                                                           double* __restrict__ cen) {
-  __shared__ double red[3 * kLossThreads];
-  double s[3] = {0.0, 0.0, 0.0};
-  for (int i0 = threadIdx.x; i0 < n; i0 += 2 * kLossThreads) {
+// Sum of part b (kCenPart landmarks) of q0: per thread the points i = t, t +
+// kLossThreads, ... in increasing i (two points' loads in flight at a time), then
+// one tree per coordinate.  The centroid is the sum of the parts in order.
+constexpr int kCenPart = 4096;
+
+__device__ __forceinline__ void center_part(const double* __restrict__ q0, int n, int b,
+                                            double s[3], double* red) {
+  const int end = min(n, (b + 1) * kCenPart);
+  for (int c = 0; c < 3; ++c) s[c] = 0.0;
+  for (int i0 = b * kCenPart + threadIdx.x; i0 < end; i0 += 2 * kLossThreads) {
     double v[2][3];
     for (int u = 0; u < 2; ++u) {
-      const int i = min(i0 + u * kLossThreads, n - 1);
+      const int i = min(i0 + u * kLossThreads, end - 1);
       for (int c = 0; c < 3; ++c) v[u][c] = q0[3 * i + c];
     }
     for (int u = 0; u < 2; ++u)
-      if (i0 + u * kLossThreads < n)
+      if (i0 + u * kLossThreads < end)
         for (int c = 0; c < 3; ++c) s[c] += v[u][c];
   }
   block_sums<3>(s, red);
-  if (threadIdx.x < 3) cen[threadIdx.x] = s[threadIdx.x] / n;
 }
 
+__global__ __launch_bounds__(kLossThreads) void k_center_parts(const double* __restrict__ q0, int n,
+                                                               double* __restrict__ part) {
+  __shared__ double red[3 * kLossThreads];
+  double s[3];
+  center_part(q0, n, blockIdx.x, s, red);
+  if (threadIdx.x < 3) part[3 * blockIdx.x + threadIdx.x] = s[threadIdx.x];
+}
+
+// Staging.  Every workgroup forms the centroid for itself: of one part from the
+// points (up to 4096 landmarks, 98 KB: a launch less, 3.6 us), else from the parts.
 template <typename R>
-__global__ __launch_bounds__(256) void k_stage(int n, const double* __restrict__ q0,
-                                               const double* __restrict__ p0,
-                                               const double* __restrict__ x,
-                                               const double* __restrict__ cen, double k,
-                                               double* __restrict__ st, double* __restrict__ xc,
-                                               Rec<R>* __restrict__ rec0) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(kLossThreads) void k_stage(
+    int n, const double* __restrict__ q0, const double* __restrict__ p0,
+    const double* __restrict__ x, double* __restrict__ cen, const double* __restrict__ part,
+    double k, double* __restrict__ st, double* __restrict__ xc, Rec<R>* __restrict__ rec0) {
+  __shared__ double red[3 * kLossThreads];
+  double s[3];
+  if (n <= kCenPart) {
+    center_part(q0, n, 0, s, red);
+  } else {
+    const int np = (n + kCenPart - 1) / kCenPart;
+    for (int c = 0; c < 3; ++c) {
+      s[c] = part[c];
+      for (int b = 1; b < np; ++b) s[c] += part[3 * b + c];
+    }
+  }
+  for (int c = 0; c < 3; ++c) s[c] = s[c] / n;
+  if (blockIdx.x == 0 && threadIdx.x < 3) cen[threadIdx.x] = s[threadIdx.x];
+  const int i = blockIdx.x * kLossThreads + threadIdx.x;
   if (i >= n) return;
   double q[3], p[3];
   for (int c = 0; c < 3; ++c) {
-    q[c] = q0[3 * i + c] - cen[c];
+    q[c] = q0[3 * i + c] - s[c];
     p[c] = p0[3 * i + c];
     st[c * n + i] = q[c];
     st[(3 + c) * n + i] = p[c];
-    if (x) xc[c * n + i] = x[3 * i + c] - cen[c];
+    if (x) xc[c * n + i] = x[3 * i + c] - s[c];
   }
   rec0[i] = make_rec<R>(k * q[0], k * q[1], k * q[2], p[0], p[1], p[2]);
 }
@@ -1434,20 +1607,18 @@ inline unsigned blocks256(int n) { return (unsigned)((n + 255) / 256); }
 // The point record's size is what the workspace layout (plan.h) assumes.
 static_assert(sizeof(Rec<float>) == 32 && sizeof(Rec<double>) == 64, "record size");
 
-hipError_t launch_centroid(const double* q0, int n, double* cen, hipStream_t s) {
-  k_centroid<<<1, kLossThreads, 0, s>>>(q0, n, cen);
-  return hipGetLastError();
-}
-
 hipError_t launch_stage(int mode, int n, const double* q0, const double* p0, const double* x,
-                        const double* cen, double k, double* st, double* xc, void* rec0,
+                        double* cen, double* part, double k, double* st, double* xc, void* rec0,
                         hipStream_t s) {
+  if (n > kCenPart)
+    k_center_parts<<<(n + kCenPart - 1) / kCenPart, kLossThreads, 0, s>>>(q0, n, part);
+  const unsigned grid = (unsigned)((n + kLossThreads - 1) / kLossThreads);
   if (mode == kFP64)
-    k_stage<double><<<blocks256(n), 256, 0, s>>>(n, q0, p0, x, cen, k, st, xc,
-                                                 static_cast<Rec<double>*>(rec0));
+    k_stage<double><<<grid, kLossThreads, 0, s>>>(n, q0, p0, x, cen, part, k, st, xc,
+                                                  static_cast<Rec<double>*>(rec0));
   else
-    k_stage<float><<<blocks256(n), 256, 0, s>>>(n, q0, p0, x, cen, k, st, xc,
-                                                static_cast<Rec<float>*>(rec0));
+    k_stage<float><<<grid, kLossThreads, 0, s>>>(n, q0, p0, x, cen, part, k, st, xc,
+                                                 static_cast<Rec<float>*>(rec0));
   return hipGetLastError();
 }
 
@@ -1504,29 +1675,45 @@ hipError_t launch_adj_step(int mode, const Plan& p, const AdjArgs& a, hipStream_
   return hipErrorInvalidValue;
 }
 
-int flow_waves(int n) {
-  static const int forced = [] {
-    const char* e = std::getenv("LDDMM_FLOW_WAVES");
-    return e ? std::atoi(e) : 0;
-  }();
-  if (forced == 1 || forced == 2 || forced == 4 || forced == 8 || forced == 16) return forced;
-  // at least 1024 landmarks per wave and step: measured best at N = 4096
-  // (W = 4 runs the 64^3-grid flow 1.2x faster than W = 1 and 1.4x faster
-  // than W = 16, whose per-step combine no longer pays)
-  int W = 1;
-  while (W < 16 && (W * 2) * 1024 <= n) W *= 2;
-  return W;
+// Eight pairs of chunks from 1024 landmarks on; at least 64 landmarks per chunk.
+void flow_chunks(FlowArgs& a) {
+  int pairs = 1;
+  while (pairs < 8 && pairs * 2 * 128 <= a.n) pairs *= 2;
+  a.pairs = pairs;
+  a.clen = ((a.n + 2 * pairs - 1) / (2 * pairs) + kFlowTile - 1) / kFlowTile * kFlowTile;
 }
 
-hipError_t launch_flow(int mode, int W, const FlowArgs& a, hipStream_t s, hipEvent_t* ev) {
+// A wave per chunk while the points leave room for it (us per step at n = 4096:
+// m = 5003 47 -> 18, 20000 48 -> 32, 100000 129 -> 112; with a wave per pair of
+// chunks and two points per lane 41, 42, 124); two points per lane where that
+// fills its rounds of 1024 workgroups at least 0.94 as well as one per lane fills
+// its rounds of 512 (m = 262144: 275 -> 242, one per lane 258).  FP64 from 768
+// workgroups on: a wave per pair (velocity at m = 262144 779 us, per chunk 842).
+// A velocity of fewer than 512 workgroups is also spread by the pairs (n =
+// 4096, m = 5003 86 -> 29 us; n = 20000, m = 1000 136 -> 81, 105 without).
+hipError_t launch_flow(int mode, const FlowArgs& args, hipStream_t s, hipEvent_t* ev) {
+  FlowArgs a = args;
   if (a.m <= 0 || a.n <= 0 || a.t1 <= a.t0 || a.slots <= 0) return hipErrorInvalidValue;
   if (a.v_out && a.t1 != a.t0 + 1) return hipErrorInvalidValue;
-  switch (mode) {
-    case kFP32: return flow_dispatch<float, false>(W, a, s, ev);
-    case kFP32Comp: return flow_dispatch<float, true>(W, a, s, ev);
-    case kFP64: return flow_dispatch<double, false>(W, a, s, ev);
+  if (mode != kFP32 && mode != kFP32Comp && mode != kFP64) return hipErrorInvalidValue;
+  const auto filled = [](int b, int round) { return (double)b / ((b + round - 1) / round * round); };
+  const int b1 = (a.m + 63) / 64, b2 = (a.m + 127) / 128;
+  const bool two = mode != kFP64 && a.pairs == 8 && b2 >= 1024 &&
+                   filled(b2, 1024) >= 0.94 * filled(b1, 512);
+  a.half = two || (mode == kFP64 && b1 >= 768) ? 0 : 1;
+  int W = a.half ? 2 * a.pairs : a.pairs;
+  dim3 grid((unsigned)(two ? b2 : b1));
+  const bool split = a.v_part && a.v_out && a.half && W > 4 && b1 < 512;
+  if (split) {
+    grid.y = (unsigned)(W / 4);
+    W = 4;
   }
-  return hipErrorInvalidValue;
+  const int rp = two ? 2 : 1;
+  const hipError_t e = mode == kFP64 ? flow_dispatch<double>(a, grid, W, rp, s, ev)
+                                     : flow_dispatch<float>(a, grid, W, rp, s, ev);
+  if (e != hipSuccess || !split) return e;
+  k_flow_sum<<<blocks256(a.m), 256, 0, s>>>(a.m, a.pairs, a.dim == 2 ? 2 : 3, a.v_part, a.v_out);
+  return hipGetLastError();
 }
 
 hipError_t launch_loss(int mode, int n, int nb, double lambda, double bscale, double rscale,
