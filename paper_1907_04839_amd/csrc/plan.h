@@ -181,6 +181,39 @@ inline RowPlan row_plan(int n, int mode) {
   return r;
 }
 
+// Row plans of the batched kernels: four waves of four rows per workgroup.
+// Measured on the solves of a server (ms, FP32-compensated, T = 40, 4 iterations;
+// eight jobs of 500 to 8000 landmarks, one of 2000, four of 1500, eight of 400):
+//   12-wave workgroups of 64 landmarks     46.7  11.6  11.7  4.88
+//   8 waves, m = 5                         43.6   4.22  8.36 4.93
+//   4 waves, m = 5                         37.2   4.25  6.73 3.88
+//   4 waves, m = 4                         39.4   3.86  6.44 3.78   (taken)
+//   2 waves, m = 5                         41.6   5.84  7.18 4.00
+// and FP64 (T = 10) 38.1, 8.90, 9.05 -> 22.8, 1.78, 3.41 (first three sets).
+// The waves share the j tiles (jg = 4), which a job alone on the chip needs (one of
+// 2000 with jg = 1: 9.5 ms); from n = 8192 on there are rows enough to fill it
+// with two and then four i-groups, whose waves share their j records.
+constexpr int kBatchWaves = 4;
+constexpr int kBatchRows = 4;
+constexpr int kBatchGrid = 2048;   // workgroups of a launch, at most
+
+inline RowPlan batch_plan(int n) {
+  RowPlan r{};
+  r.m = kBatchRows;
+  r.jg = n < 8192 ? 4 : n < 16384 ? 2 : 1;
+  r.ig = kBatchWaves / r.jg;
+  r.groups = (n + r.m * r.ig - 1) / (r.m * r.ig);
+  return r;
+}
+
+// The most workgroups that a job of at most max_n landmarks has.
+inline int batch_groups(int max_n) {
+  int g = batch_plan(max_n).groups;
+  for (const int n : {8191, 16383})
+    if (n < max_n && batch_plan(n).groups > g) g = batch_plan(n).groups;
+  return g;
+}
+
 inline Scales make_scales(double sigma, int T) {
   Scales s{};
   const double log2e = 1.4426950408889634;

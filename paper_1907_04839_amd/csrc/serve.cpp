@@ -8,7 +8,7 @@
 // and one optimiser step per round, as one replay of a captured hipGraph:
 // batched stage, T forward pair-sum launches, batched loss, T adjoint
 // launches, batched L-BFGS step.  Each pair-sum launch covers every
-// (job, 64-landmark i-block) item of its kind (once planar jobs have come,
+// (job, group of rows) item of its kind (once planar jobs have come,
 // each step has a launch for the 3D items and one for the planar items,
 // which leave the z terms out), so small jobs share the chip instead of
 // leaving it idle.  Jobs join at the next round after admission and leave
@@ -60,7 +60,7 @@ struct ServerJob {
 
 // Byte layout of one job inside its arena block.
 struct JobLayout {
-  size_t q0, x, cen, st, ad, hp0, xc, h0p, out3, traj, arec, q1, vec, hist, state, out3a, q1a;
+  size_t q0, x, cen, st, ad, hp0, xc, out3, traj, arec, q1, vec, hist, state, out3a, q1a;
   size_t rk_acc, rk_lam;
   size_t total;
 };
@@ -70,7 +70,7 @@ size_t a256(size_t b) { return (b + 255) & ~size_t(255); }
 // spt: point records per step, 1 for Euler steps, 4 for Runge-Kutta stages.
 JobLayout job_layout(int n, int T, int precision, int m, int spt) {
   JobLayout L{};
-  const size_t N = (size_t)n, m3 = 3 * N, rb = rec_bytes(precision), nb = (N + 63) / 64;
+  const size_t N = (size_t)n, m3 = 3 * N, rb = rec_bytes(precision);
   size_t off = 0;
   auto take = [&](size_t b) { size_t o = off; off += a256(b); return o; };
   L.q0 = take(m3 * 8);
@@ -80,7 +80,6 @@ JobLayout job_layout(int n, int T, int precision, int m, int spt) {
   L.ad = take(6 * N * 8);
   L.hp0 = take(m3 * 8);
   L.xc = take(m3 * 8);
-  L.h0p = take(nb * 8);
   L.out3 = take(4 * 8);
   L.traj = take(((size_t)spt * T + 1) * N * rb);
   L.arec = take(2 * N * rb);
@@ -222,7 +221,7 @@ bool admit(lddmm_server* s, ServerJob* j, int k) {
   BatchJob b{};
   b.active = 1;
   b.n = n;
-  b.nb = (n + 63) / 64;
+  b.row = batch_plan(n);
   b.lambda = j->p.lambda;
   b.sc = sc;
   b.q0 = q0;
@@ -231,7 +230,9 @@ bool admit(lddmm_server* s, ServerJob* j, int k) {
   b.ad = at<double>(base, L.ad);
   b.hp0 = at<double>(base, L.hp0);
   b.xc = at<double>(base, L.xc);
-  b.h0p = at<double>(base, L.h0p);
+  // a partial per workgroup, in adjoint record buffer 1, which the first adjoint
+  // launch writes after the loss has read them
+  b.h0p = at<double>(base, L.arec + (size_t)n * rec_bytes(mode));
   b.out3 = at<double>(base, L.out3);
   b.traj = at<void>(base, L.traj);
   b.arec = at<void>(base, L.arec);
@@ -293,7 +294,7 @@ bool upload_tables(lddmm_server* s, int parity) {
                      [&](int a, int b) { return s->tab[a].n > s->tab[b].n; });
     const int first = ni;
     for (int k : order)
-      for (int ib = 0; ib < s->tab[k].nb; ++ib) s->h_items[parity][ni++] = make_int2(k, ib);
+      for (int g = 0; g < s->tab[k].row.groups; ++g) s->h_items[parity][ni++] = make_int2(k, g);
     s->h_nitems[parity][dim == 3 ? 0 : 1] = ni - first;
     if (ni > first) s->dims_seen |= dim == 3 ? 1 : 2;
   }
@@ -522,7 +523,7 @@ lddmm_status lddmm_server_create(const lddmm_server_config* cfg, lddmm_server** 
   s->cfg = *cfg;
   s->t0 = Clock::now();
   const int M = cfg->max_slots;
-  s->capacity = M * ((cfg->max_n + 63) / 64);
+  s->capacity = M * batch_groups(cfg->max_n);
   s->tab.assign(M, BatchJob{});
   s->ltab.assign(M, LbfgsJob{});
   s->slot_job.assign(M, nullptr);

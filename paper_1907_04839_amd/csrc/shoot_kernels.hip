@@ -653,11 +653,12 @@ __device__ __forceinline__ int row_at(int k) {
   return (k / M) * row_pad<D, M> + (k % M) * 2 * D;
 }
 
-// Sums of one wave: rows i0 .. i0 + M - 1 over the tiles t = jg, jg + JG, ...
+// Sums of one wave: rows i0 .. i0 + M - 1 over the tiles t = t0, t0 + JG, ... < t1.
 // ADJ: h[m] = {A1 / kappa - A2 (D components), B (D)}, else {Hp (D), Hq's sums (D)}.
 template <typename R, bool ADJ, int D, int M>
-__device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, int i0, int jg,
-                                         int JG, int lane, R inv_kappa, R h[row_pad<D, M>]) {
+__device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, int i0, int t0,
+                                         int t1, int JG, int lane, R inv_kappa,
+                                         R h[row_pad<D, M>]) {
   const GlobalPtr<Rec<R>> X = global_ptr(static_cast<const Rec<R>*>(Xv));
   const GlobalPtr<Rec<R>> Y = global_ptr(static_cast<const Rec<R>*>(Yv));
   R xi[M][6], yi[M][6];
@@ -675,17 +676,30 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
   }
 #pragma unroll
   for (int k = 0; k < row_pad<D, M>; ++k) h[k] = (R)0;
-  const int nt = (n + 63) >> 6;
-  for (int t = jg; t < nt; t += JG) {
-    const bool in = t * 64 + lane < n;
-    const int j = in ? t * 64 + lane : n - 1;
-    const Vec3<R>* xp = reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Xv)[j].x);
-    const Vec3<R>* pp = reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Xv)[j].px);
-    Vec3<R> q = *xp, p = *pp, a = (R)0, b = (R)0;
+  struct Tile { Vec3<R> q, p, a, b; };
+  const auto load = [&](int j) {
+    Tile r;
+    const GlobalPtr<Rec<R>> x = X + j;
+    r.q = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&x->x);
+    r.p = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&x->px);
     if constexpr (ADJ) {
-      a = *reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Yv)[j].x);
-      b = *reinterpret_cast<const Vec3<R>*>(&static_cast<const Rec<R>*>(Yv)[j].px);
+      const GlobalPtr<Rec<R>> y = Y + j;
+      r.a = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&y->x);
+      r.b = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&y->px);
     }
+    return r;
+  };
+  // one tile ahead (the last one twice): with few waves per SIMD the loads'
+  // latency shows (FP64, n = 2500: adjoint 21.6 us per step without, 19.9 with)
+  int j = t0 * 64 + lane;
+  Tile next = load(min(j, n - 1));
+  for (int t = t0; t < t1; t += JG) {
+    const bool in = j < n;
+    const Tile cur = next;
+    j += 64 * JG;
+    next = load(min(j, n - 1));
+    Vec3<R> q = cur.q, p = cur.p, a = (R)0, b = (R)0;
+    if constexpr (ADJ) { a = cur.a; b = cur.b; }
     if (!in) { q = (R)0; p = (R)0; a = (R)0; b = (R)0; }   // adds an exact 0 to every sum
     Vec3<R> ps = p;
     if constexpr (ADJ) ps = p * inv_kappa;
@@ -734,10 +748,11 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
   }
 }
 
-// The workgroup's sums of rows [0, kRows ig) in fin[row][2 D], from every wave's h.
+// The workgroup's sums of rows [0, M ig) in fin (row_at), from every wave's h;
+// added to what fin holds with `add`.
 template <typename R, int D, int M>
 __device__ __forceinline__ void row_combine(R h[row_pad<D, M>], R* red, double* fin, int ig, int jg,
-                                            int w, int lane) {
+                                            int w, int lane, bool add) {
   constexpr int NV = row_pad<D, M>, Q = NV / 4;
   R* f = h;
 #pragma unroll
@@ -756,25 +771,35 @@ __device__ __forceinline__ void row_combine(R h[row_pad<D, M>], R* red, double* 
     s = row_add<0x122>(s);
     s = row_add<0x124>(s);
     s = row_add<0x128>(s);
-    if ((lane & 15) == 0) fin[g * NV + k + Q * (lane >> 4)] = s;
+    if ((lane & 15) == 0) {
+      double* f = fin + g * NV + k + Q * (lane >> 4);
+      *f = add ? *f + s : s;
+    }
   }
   __syncthreads();
 }
 
-template <typename R, bool RKS, int D, int M>
-__global__ __launch_bounds__(64 * kRowWaves<R>) void k_fwd_rows(FwdArgs A) {
-  __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
-  __shared__ double fin[kRowGroups * row_pad<D, M>];
+// A step of the rows of workgroup item g, in ig x jg waves.  BATCH: n may be
+// large, so a wave's tiles are taken kTile at a time and no FP32 sum is longer
+// than kTile terms; the row plans end before that, and with the loop around them
+// their adjoint took 10 % longer (n = 1847).
+template <typename R, bool RKS, int D, int M, bool BATCH = false>
+__device__ __forceinline__ void fwd_rows(const FwdArgs& A, int g, R* red, double* fin) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int row0 = blockIdx.x * A.ig * M;
-  R h[row_pad<D, M>];
+  const int row0 = g * A.ig * M, nt = (A.n + 63) >> 6;
   FwdState v{};
-  if (w == 0) v = load_fwd_state<RKS>(A, row0 + lane);   // its latency under the sums
-  row_sums<R, false, D, M>(A.rec_t, nullptr, A.n, row0 + (w % A.ig) * M, w / A.ig, A.jg, lane,
-                        (R)0, h);
-  row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane);
+  if (!BATCH && w == 0) v = load_fwd_state<RKS>(A, row0 + lane);   // its latency under the sums
+  const int step = BATCH ? kTile * A.jg : nt;
+  for (int t0 = 0; t0 < nt; t0 += step) {
+    R h[row_pad<D, M>];
+    row_sums<R, false, D, M>(A.rec_t, nullptr, A.n, row0 + (w % A.ig) * M, t0 + w / A.ig,
+                             BATCH ? min(nt, t0 + step) : nt, A.jg, lane, (R)0, h);
+    row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane, BATCH && t0 > 0);
+    if (!BATCH) break;
+  }
   if (w == 0) {
+    if (BATCH) v = load_fwd_state<RKS>(A, row0 + lane);
     const bool own = lane < A.ig * M && row0 + lane < A.n;
     double hp[3] = {0.0, 0.0, 0.0}, hq[3] = {0.0, 0.0, 0.0};
     if (own)
@@ -782,24 +807,27 @@ __global__ __launch_bounds__(64 * kRowWaves<R>) void k_fwd_rows(FwdArgs A) {
         hp[c] = fin[row_at<D, M>(lane) + c];
         hq[c] = fin[row_at<D, M>(lane) + D + c];
       }
-    fwd_finish<R, RKS>(A, row0 + lane, own, blockIdx.x, lane, v, hp, hq);
+    fwd_finish<R, RKS>(A, row0 + lane, own, g, lane, v, hp, hq);
   }
 }
 
-template <typename R, bool RKS, int D, int M>
-__global__ __launch_bounds__(64 * kRowWaves<R>) void k_adj_rows(AdjArgs A) {
-  __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
-  __shared__ double fin[kRowGroups * row_pad<D, M>];
+template <typename R, bool RKS, int D, int M, bool BATCH = false>
+__device__ __forceinline__ void adj_rows(const AdjArgs& A, int g, R* red, double* fin) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int row0 = blockIdx.x * A.ig * M;
-  R h[row_pad<D, M>];
+  const int row0 = g * A.ig * M, nt = (A.n + 63) >> 6;
   AdjState v{};
-  if (w == 0) v = load_adj_state<RKS>(A, row0 + lane);   // its latency under the sums
-  row_sums<R, true, D, M>(A.rec_t, A.arec, A.n, row0 + (w % A.ig) * M, w / A.ig, A.jg, lane,
-                       (R)(1.0 / A.sc.kappa), h);
-  row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane);
+  if (!BATCH && w == 0) v = load_adj_state<RKS>(A, row0 + lane);   // its latency under the sums
+  const int step = BATCH ? kTile * A.jg : nt;
+  for (int t0 = 0; t0 < nt; t0 += step) {
+    R h[row_pad<D, M>];
+    row_sums<R, true, D, M>(A.rec_t, A.arec, A.n, row0 + (w % A.ig) * M, t0 + w / A.ig,
+                            BATCH ? min(nt, t0 + step) : nt, A.jg, lane, (R)(1.0 / A.sc.kappa), h);
+    row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane, BATCH && t0 > 0);
+    if (!BATCH) break;
+  }
   if (w == 0 && lane < A.ig * M && row0 + lane < A.n) {
+    if (BATCH) v = load_adj_state<RKS>(A, row0 + lane);
     double sa[3] = {0.0, 0.0, 0.0}, sb[3] = {0.0, 0.0, 0.0};
     for (int c = 0; c < D; ++c) {
       sa[c] = fin[row_at<D, M>(lane) + c];
@@ -807,6 +835,20 @@ __global__ __launch_bounds__(64 * kRowWaves<R>) void k_adj_rows(AdjArgs A) {
     }
     adj_finish<R, RKS>(A, row0 + lane, v, sa, sb);
   }
+}
+
+template <typename R, bool RKS, int D, int M>
+__global__ __launch_bounds__(64 * kRowWaves<R>) void k_fwd_rows(FwdArgs A) {
+  __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
+  __shared__ double fin[kRowGroups * row_pad<D, M>];
+  fwd_rows<R, RKS, D, M>(A, blockIdx.x, red, fin);
+}
+
+template <typename R, bool RKS, int D, int M>
+__global__ __launch_bounds__(64 * kRowWaves<R>) void k_adj_rows(AdjArgs A) {
+  __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
+  __shared__ double fin[kRowGroups * row_pad<D, M>];
+  adj_rows<R, RKS, D, M>(A, blockIdx.x, red, fin);
 }
 
 // ---------------------------------------------------------------------------
@@ -1140,10 +1182,10 @@ __device__ __forceinline__ void gather_partials(const Acc* __restrict__ P, int n
 
 // One wave per i-block and latency-bound: let the scheduler spend registers
 // on loads in flight rather than on occupancy.
-#define LDDMM_LATENCY_BOUND __attribute__((amdgpu_waves_per_eu(1, 2)))
+#define LDDMM_BATCHNCY_BOUND __attribute__((amdgpu_waves_per_eu(1, 2)))
 
 template <typename R, bool COMP, int SC, bool RKS>
-__global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_fwd_update(FwdArgs A) {
+__global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_fwd_update(FwdArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   const int ib = blockIdx.x, lane = threadIdx.x;
   const FwdState v = load_fwd_state<RKS>(A, ib * 64 + lane);
@@ -1154,7 +1196,7 @@ __global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_fwd_update(FwdArgs A
 }
 
 template <typename R, bool COMP, int SC, bool RKS>
-__global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_adj_update(AdjArgs A) {
+__global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_adj_update(AdjArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   const int ib = blockIdx.x, lane = threadIdx.x;
   const AdjState v = load_adj_state<RKS>(A, ib * 64 + lane);
@@ -1169,7 +1211,7 @@ __global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_adj_update(AdjArgs A
 // second memory round trip.  Wave 1 sums components 5-8 (in chunk order, as
 // above) and hands them over through LDS; wave 0 sums 0-4 and finishes.
 template <typename R, bool COMP, int SC, bool RKS>
-__global__ __launch_bounds__(128) LDDMM_LATENCY_BOUND void k_adj_update2(AdjArgs A) {
+__global__ __launch_bounds__(128) LDDMM_BATCHNCY_BOUND void k_adj_update2(AdjArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   __shared__ double red[4 * 64];
   const int ib = blockIdx.x, lane = threadIdx.x & 63;
@@ -1426,10 +1468,10 @@ __global__ __launch_bounds__(256) void k_stage_batch(const BatchJob* __restrict_
 // stage: 0 for an Euler step, else Runge-Kutta stage 1..4 of step t.  Record
 // r = spt t + stage - 1 (stage 0: r = t) is read, record r + 1 written (the
 // next stage's state, or after the last stage the state of step t + 1).
-template <typename R, int D, int BW>
+template <typename R, int D>
 __device__ __forceinline__ FwdArgs batch_fwd_args(const BatchJob& b, int t, int stage) {
   FwdArgs A{};
-  A.n = b.n; A.nb = b.nb; A.S = 1; A.chunk = b.n; A.wchunk = (b.n + BW - 1) / BW;
+  A.n = b.n; A.ig = b.row.ig; A.jg = b.row.jg;
   A.dim = D;
   A.rk = stage;
   A.rk_acc = b.rk_acc;
@@ -1444,46 +1486,13 @@ __device__ __forceinline__ FwdArgs batch_fwd_args(const BatchJob& b, int t, int 
   return A;
 }
 
-// Work items: nitems[0] items of 3D jobs, then nitems[1] items of planar jobs;
-// the D = 3 instance takes the first group, the D = 2 instance the second.
-template <int D>
-__device__ __forceinline__ bool batch_item(const int2* __restrict__ items,
-                                           const int* __restrict__ nitems, int2* it) {
-  const int count = nitems[D == 2 ? 1 : 0];
-  if ((int)blockIdx.x >= count) return false;
-  *it = items[(D == 2 ? nitems[0] : 0) + (int)blockIdx.x];
-  return true;
-}
-
-// BW: waves per workgroup (batch_waves).
-template <typename R, bool COMP, bool RKS, int D, int BW>
-__global__ __launch_bounds__(64 * BW) void k_fwd_batch(const BatchJob* __restrict__ J,
-                                                                const int2* __restrict__ items,
-                                                                const int* __restrict__ nitems,
-                                                                int t, int stage) {
-  __shared__ typename AccOf<R, COMP>::type red[BW * 6 * 64];
-  int2 it;
-  if (!batch_item<D>(items, nitems, &it)) return;
-  const BatchJob& b = J[it.x];
-  if (!job_live(b)) return;
-  fwd_block<R, COMP, RKS, BW, D>(batch_fwd_args<R, D, BW>(b, t, stage), it.y, 0, red);
-}
-
 // Adjoint launches run t = T-1 .. 0 (and stages 4 .. 1 within a Runge-Kutta
 // step); the loss kernel fills adjoint record buffer 0 for the first of them,
 // and each launch reads buffer (launch index & 1) and writes the other.
-template <typename R, bool COMP, bool RKS, int D, int BW>
-__global__ __launch_bounds__(64 * BW) void k_adj_batch(const BatchJob* __restrict__ J,
-                                                                const int2* __restrict__ items,
-                                                                const int* __restrict__ nitems,
-                                                                int t, int stage, int T) {
-  __shared__ typename AccOf<R, COMP>::type red[BW * 9 * 64];
-  int2 it;
-  if (!batch_item<D>(items, nitems, &it)) return;
-  const BatchJob& b = J[it.x];
-  if (!job_live(b)) return;
+template <typename R, int D>
+__device__ __forceinline__ AdjArgs batch_adj_args(const BatchJob& b, int t, int stage, int T) {
   AdjArgs A{};
-  A.n = b.n; A.nb = b.nb; A.S = 1; A.chunk = b.n; A.wchunk = (b.n + BW - 1) / BW;
+  A.n = b.n; A.ig = b.row.ig; A.jg = b.row.jg;
   A.dim = D;
   A.rk = stage;
   A.rk_lam = b.rk_lam;
@@ -1497,7 +1506,36 @@ __global__ __launch_bounds__(64 * BW) void k_adj_batch(const BatchJob* __restric
   A.ad = b.ad;
   A.hp0 = b.hp0;
   A.grad = t == 0 && stage <= 1 ? b.grad : nullptr;
-  adj_block<R, COMP, RKS, BW, D>(A, it.y, 0, red);
+  return A;
+}
+
+// Work items: nitems[0] items of 3D jobs, then nitems[1] items of planar jobs;
+// the D = 3 instance takes the first group, the D = 2 instance the second.  An
+// item is one workgroup's rows of a job (row kernels); workgroup b of G takes the
+// items b, b + G, ...  The items come with the largest jobs first, so what is
+// left to balance at the end are short ones; the state is loaded after the sums
+// (other workgroups cover its latency, and the registers are worth more).  FP32's
+// occupancy is what its registers allow without spills.  What bounds it: issue.
+// Eight jobs of 500 to 8000 landmarks took 77 and 146 us per forward and adjoint
+// step with a workgroup per 64 landmarks, whose uneven lengths left half the chip
+// idle (41 and 81 us at the rate of the 65536-landmark kernels).
+template <typename R, int D, bool ADJ, bool RKS>
+__global__ __launch_bounds__(64 * kBatchWaves,
+                             sizeof(R) == 8 ? 1 : ADJ ? 4 : 5) void k_batch(const BatchJob* __restrict__ J,
+                                                            const int2* __restrict__ items,
+                                                            const int* __restrict__ nitems, int t,
+                                                            int stage, int T) {
+  constexpr int M = kBatchRows;
+  __shared__ R red[kBatchWaves * (row_pad<D, M> / 4) * 64];
+  __shared__ double fin[kBatchWaves * row_pad<D, M>];
+  const int2* it = items + (D == 2 ? nitems[0] : 0);
+  const int count = nitems[D == 2 ? 1 : 0];
+  for (int k = blockIdx.x; k < count; k += gridDim.x) {
+    const BatchJob& b = J[it[k].x];
+    if (!job_live(b)) continue;
+    if constexpr (ADJ) adj_rows<R, RKS, D, M, true>(batch_adj_args<R, D>(b, t, stage, T), it[k].y, red, fin);
+    else fwd_rows<R, RKS, D, M, true>(batch_fwd_args<R, D>(b, t, stage), it[k].y, red, fin);
+  }
 }
 
 template <typename R>
@@ -1505,7 +1543,7 @@ __global__ __launch_bounds__(kLossThreads) void k_loss_batch(const BatchJob* __r
   __shared__ double red[2 * kLossThreads];
   const BatchJob& b = J[blockIdx.x];
   if (!job_live(b)) return;
-  loss_body<R>(b.n, b.nb, b.lambda, b.st, b.xc, b.cen, b.h0p, b.ad, static_cast<Rec<R>*>(b.arec),
+  loss_body<R>(b.n, b.row.groups, b.lambda, b.st, b.xc, b.cen, b.h0p, b.ad, static_cast<Rec<R>*>(b.arec),
                b.out3, b.q1, nullptr, b.flag, nullptr, nullptr, nullptr, 0.0,
                b.spt == 4 ? b.sc.dt / 6.0 : 1.0, red);
 }
@@ -1747,62 +1785,37 @@ hipError_t launch_stage_batch(int mode, const BatchJob* jobs, int max_slots, int
   return hipGetLastError();
 }
 
-template <typename R, bool COMP, int D>
-void fwd_batch_dispatch(const BatchJob* jobs, const int2* items, const int* nitems, int capacity,
-                        int t, int stage, hipStream_t s) {
-  constexpr int EW = batch_waves(COMP, false), RW = batch_waves(COMP, true);
-  if (stage > 0)
-    k_fwd_batch<R, COMP, true, D, RW><<<capacity, 64 * RW, 0, s>>>(jobs, items, nitems, t, stage);
-  else k_fwd_batch<R, COMP, false, D, EW><<<capacity, 64 * EW, 0, s>>>(jobs, items, nitems, t, 0);
+template <typename R, int D, bool ADJ>
+void batch_dispatch(const BatchJob* jobs, const int2* items, const int* nitems, int capacity,
+                    int t, int stage, int T, hipStream_t s) {
+  constexpr int kThreads = 64 * kBatchWaves;
+  const int grid = min(capacity, kBatchGrid);
+  if (stage > 0) k_batch<R, D, ADJ, true><<<grid, kThreads, 0, s>>>(jobs, items, nitems, t, stage, T);
+  else k_batch<R, D, ADJ, false><<<grid, kThreads, 0, s>>>(jobs, items, nitems, t, 0, T);
 }
 
-template <typename R, bool COMP, int D>
-void adj_batch_dispatch(const BatchJob* jobs, const int2* items, const int* nitems, int capacity,
-                        int t, int stage, int T, hipStream_t s) {
-  constexpr int EW = batch_waves(COMP, false), RW = batch_waves(COMP, true);
-  if (stage > 0)
-    k_adj_batch<R, COMP, true, D, RW><<<capacity, 64 * RW, 0, s>>>(jobs, items, nitems, t, stage,
-                                                                    T);
-  else k_adj_batch<R, COMP, false, D, EW><<<capacity, 64 * EW, 0, s>>>(jobs, items, nitems, t, 0, T);
-}
-
-template <int D>
-hipError_t fwd_batch_mode(int mode, const BatchJob* jobs, const int2* items, const int* nitems,
-                          int capacity, int t, int stage, hipStream_t s) {
-  switch (mode) {
-    case kFP32: fwd_batch_dispatch<float, false, D>(jobs, items, nitems, capacity, t, stage, s); break;
-    case kFP32Comp: fwd_batch_dispatch<float, true, D>(jobs, items, nitems, capacity, t, stage, s); break;
-    case kFP64: fwd_batch_dispatch<double, false, D>(jobs, items, nitems, capacity, t, stage, s); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-template <int D>
-hipError_t adj_batch_mode(int mode, const BatchJob* jobs, const int2* items, const int* nitems,
-                          int capacity, int t, int stage, int T, hipStream_t s) {
-  switch (mode) {
-    case kFP32: adj_batch_dispatch<float, false, D>(jobs, items, nitems, capacity, t, stage, T, s); break;
-    case kFP32Comp: adj_batch_dispatch<float, true, D>(jobs, items, nitems, capacity, t, stage, T, s); break;
-    case kFP64: adj_batch_dispatch<double, false, D>(jobs, items, nitems, capacity, t, stage, T, s); break;
-    default: return hipErrorInvalidValue;
-  }
+template <bool ADJ>
+hipError_t launch_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
+                        const int* nitems, int capacity, int t, int stage, int T, hipStream_t s) {
+  if (dim != 2 && dim != 3) return hipErrorInvalidValue;
+  const bool f64 = mode == kFP64;
+  if (f64 && dim == 3)
+    batch_dispatch<double, 3, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
+  else if (f64) batch_dispatch<double, 2, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
+  else if (dim == 3) batch_dispatch<float, 3, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
+  else batch_dispatch<float, 2, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
   return hipGetLastError();
 }
 
 hipError_t launch_fwd_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
                             const int* nitems, int capacity, int t, int stage, hipStream_t s) {
-  if (dim == 2) return fwd_batch_mode<2>(mode, jobs, items, nitems, capacity, t, stage, s);
-  if (dim == 3) return fwd_batch_mode<3>(mode, jobs, items, nitems, capacity, t, stage, s);
-  return hipErrorInvalidValue;
+  return launch_batch<false>(mode, dim, jobs, items, nitems, capacity, t, stage, 0, s);
 }
 
 hipError_t launch_adj_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
                             const int* nitems, int capacity, int t, int stage, int T,
                             hipStream_t s) {
-  if (dim == 2) return adj_batch_mode<2>(mode, jobs, items, nitems, capacity, t, stage, T, s);
-  if (dim == 3) return adj_batch_mode<3>(mode, jobs, items, nitems, capacity, t, stage, T, s);
-  return hipErrorInvalidValue;
+  return launch_batch<true>(mode, dim, jobs, items, nitems, capacity, t, stage, T, s);
 }
 
 hipError_t launch_loss_batch(int mode, const BatchJob* jobs, int max_slots, hipStream_t s) {

@@ -35,6 +35,17 @@ int main() {
       CHECK((size_t)r.groups * 8 <= (size_t)n * lddmm::rec_bytes(mode), n);   // H0 partials fit
     }
   CHECK(taken == 2 * 5120 + 3072, taken);
+  // the batched kernels' plans, and the room that a server reserves for them
+  int most = 0;
+  for (int n = 1; n <= 40000; ++n) {
+    const lddmm::RowPlan r = lddmm::batch_plan(n);
+    const int rows = r.ig * r.m;
+    CHECK(r.m == lddmm::kBatchRows && r.ig * r.jg == lddmm::kBatchWaves, n);
+    CHECK(r.groups * rows >= n && (r.groups - 1) * rows < n, n);
+    CHECK((size_t)r.groups * 8 <= (size_t)n * lddmm::rec_bytes(lddmm::kFP32), n);
+    most = r.groups > most ? r.groups : most;
+    CHECK(lddmm::batch_groups(n) == most, n);
+  }
   std::printf("row plans ok (%d)\n", taken);
   return 0;
 }

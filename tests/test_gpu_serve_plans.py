@@ -1,0 +1,43 @@
+"""The batched row kernels at the sizes where a job's plan changes, against the
+oracle's solver.
+
+One optimiser iteration from p0 = 0 leaves a multiple of the first gradient in
+p0, so its direction is compared as a gradient is; tolerances are the library's
+bars, 1e-12 for FP64 sums and 1e-5 for FP32 ones (and 1e-10 where an FP64 step
+length enters, as in the solver's own tests).  Sizes: below one row group, one
+tile of 64 and its neighbours, the last and first size of each share of the j
+tiles (8191 | 8192, 16383 | 16384), and ones where a wave's tiles exceed 72 and are
+summed in several rounds (above 9216 with two waves to the tiles, always with
+one)."""
+import numpy as np
+import pytest
+
+from paper_1907_04839_amd import synth
+
+from conftest import rel_err, row_err
+
+pytestmark = pytest.mark.gpu
+CASES = [("fp32c", n) for n in (1, 3, 64, 65, 257, 8191, 8192, 9300, 16383, 16385)]
+CASES += [("fp64", n) for n in (1, 5, 65, 8193, 16385)] + [("fp32", 65), ("fp32", 16385)]
+CASES += [("planar", 130), ("planar", 9300)]
+
+
+@pytest.mark.parametrize("mode,n", CASES)
+def test_served_step_matches_oracle(orc_mt, mode, n):
+    from paper_1907_04839_amd import lddmm
+    T = 1
+    pb = synth.random_problem(7000 + n, n, T=T)
+    dim = 3
+    if mode == "planar":
+        pb, dim, mode = synth.planar(pb), 2, "fp32c"
+    with lddmm.Server(T, mode, max_slots=2, max_n=20000, hbm_budget_bytes=128 << 20) as s:
+        jid = s.submit(pb.q0, pb.target, pb.sigma, pb.lam, max_iter=1, dim=dim)
+        r = s.result(jid, timeout=120)
+    o = orc_mt.solve(pb.q0, pb.target, pb.sigma, pb.lam, T, orc_mt.SolveOpts(max_iter=1))
+    assert r["iters"] == o["iters"] and r["fevals"] == o["fevals"]
+    a, b = r["p0"] / np.linalg.norm(r["p0"]), o["p0"] / np.linalg.norm(o["p0"])
+    direction = max(rel_err(a, b), row_err(a, b))
+    loss = abs(r["loss"] - o["loss"]) / o["loss"]
+    print(f"[serve {mode} d{dim} n={n}] direction={direction:.1e} loss={loss:.1e}", flush=True)
+    assert direction <= (1e-12 if mode == "fp64" else 1e-5)
+    assert loss <= (1e-10 if mode == "fp64" else 1e-5)
