@@ -215,6 +215,7 @@ Plan plan_for(const lddmm_params& p) {
   if (!plan_overridden()) {
     widen_plan(plan, p.precision, p.integrator == LDDMM_RK4);
     plan.row = row_plan(p.n, p.precision);
+    plan.chain = p.n <= kChainMax;
   }
   return plan;
 }
@@ -258,12 +259,42 @@ Job make_job(const lddmm_params& p, void* ws) {
   return j;
 }
 
+// Steps [t0, t1) as the chain kernels take them, at most kChainSteps per launch.
+constexpr int kChainSteps = 4096;
+ChainArgs chain_args(const Job& j, int t0, int t1) {
+  ChainArgs c{};
+  c.t0 = t0; c.t1 = t1; c.T = j.p.T;
+  c.spt = j.spt;
+  c.slots = j.L.nseg > 0 ? j.L.slots : 0;
+  c.nh = j.nh;
+  c.traj = j.traj;
+  c.h0_part = j.h0p;
+  c.ckpt = j.ckpt;
+  return c;
+}
+
 // Forward steps t in [t0, t1): one launch per Euler step, four per Runge-Kutta
 // step (its stages).  first: capture Hp(q0,p0) and H0 at t == 0.
 hipError_t run_forward(const Job& j, int t0, int t1, bool first, bool store_ckpt, hipStream_t s,
                        Timer* tm, bool want_hq0 = false) {
   const int mode = j.p.precision;
   const int stages = j.spt;
+  if (j.plan.chain) {
+    for (int t = t0; t < t1; t += kChainSteps) {
+      ChainArgs c = chain_args(j, t, std::min(t1, t + kChainSteps));
+      c.first = first;
+      c.every = store_ckpt && j.L.nseg > 0 ? j.p.ckpt_every : 0;
+      FwdArgs a{};
+      a.n = j.p.n; a.dim = j.dim; a.sc = j.sc;
+      a.rk_acc = j.rk_acc;
+      a.st = j.st;
+      a.hp0 = j.hp0;
+      a.hq0 = want_hq0 ? j.hq0 : nullptr;
+      hipError_t e = launch_fwd_chain(mode, c, a, s, tm->take(0));
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   for (int t = t0; t < t1; ++t) {
     for (int st = 0; st < stages; ++st) {
       const bool last = st == stages - 1;   // this launch writes the state of step t + 1
@@ -299,6 +330,26 @@ hipError_t run_adjoint(const Job& j, int t0, int t1, int* cur, double* grad, hip
                        Timer* tm, double* grad_q0 = nullptr) {
   const int mode = j.p.precision;
   const int stages = j.spt;
+  if (j.plan.chain) {
+    const bool fin = j.p.energy == LDDMM_ENERGY_FINAL;   // as below
+    for (int t = t1; t > t0; t -= kChainSteps) {
+      const ChainArgs c = chain_args(j, std::max(t0, t - kChainSteps), t);
+      AdjArgs a{};
+      a.n = j.p.n; a.dim = j.dim; a.sc = j.sc;
+      a.rk_lam = j.rk_lam;
+      a.arec = j.arec_buf(*cur);
+      a.arec_next = j.arec_buf(*cur ^ 1);
+      a.ad = j.ad;
+      a.hp0 = fin ? nullptr : j.hp0;
+      a.grad = grad;
+      a.hq0 = fin ? nullptr : j.hq0;
+      a.grad_q0 = grad_q0;
+      hipError_t e = launch_adj_chain(mode, c, a, s, tm->take(1));
+      if (e != hipSuccess) return e;
+      *cur ^= (c.t1 - c.t0) * stages & 1;
+    }
+    return hipSuccess;
+  }
   for (int t = t1 - 1; t >= t0; --t) {
     for (int st = stages - 1; st >= 0; --st) {
       AdjArgs a{};

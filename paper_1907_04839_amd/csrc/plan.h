@@ -39,6 +39,7 @@ struct Plan {
   int Wa;       // waves per workgroup of the adjoint pair kernel
   int wchunk_a; // j per wave of the adjoint pair kernel
   RowPlan row;  // m > 0: the row kernels take the step instead
+  bool chain;   // one launch takes all steps (then row is set too)
 };
 
 // Coordinates enter the pair kernels pre-scaled by k = sqrt(log2(e) / (2 sigma^2)),
@@ -180,6 +181,10 @@ inline RowPlan row_plan(int n, int mode) {
   r.groups = groups(r.m * r.ig);
   return r;
 }
+
+// The chain kernels take the sizes that one landmark per lane of a wave holds; their
+// comment has the figures on both sides of the line.
+constexpr int kChainMax = 64;
 
 // Row plans of the batched kernels: four waves of four rows per workgroup.
 // Measured on the solves of a server (ms, FP32-compensated, T = 40, 4 iterations;

@@ -56,6 +56,31 @@ struct AdjArgs {
   void* partial;        // [S][9][n] partial sums when S > 1
 };
 
+// All steps [t0, t1) of a small problem in one launch (Plan::chain); the arguments
+// of the single steps follow from these and the step's own.
+struct ChainArgs {
+  int t0, t1, T;
+  int spt;              // records per step: 1 (Euler), 4 (Runge-Kutta stages)
+  int slots;            // the trajectory is a ring of so many records (0: it is whole)
+  int first;            // capture Hp, Hq and H0 at t == 0 (forward)
+  int every;            // forward: a checkpoint every so many steps (0: none)
+  int nh;               // H0 partials (the forward writes all of them)
+  char* traj;
+  double* h0_part;
+  double* ckpt;         // [segments][6][n]
+  __host__ __device__ void* rec(int t, int stage, int n, size_t rb) const {
+    const int r = spt * t + stage;
+    return traj + (size_t)(slots > 0 ? r % slots : r) * n * rb;
+  }
+  __host__ __device__ double* ckpt_of(int t, int n) const {
+    return every > 0 && t % every == 0 && t < T ? ckpt + (size_t)(t / every) * 6 * n : nullptr;
+  }
+};
+hipError_t launch_fwd_chain(int mode, const ChainArgs& c, const FwdArgs& a, hipStream_t s,
+                            hipEvent_t* ev = nullptr);
+hipError_t launch_adj_chain(int mode, const ChainArgs& c, const AdjArgs& a, hipStream_t s,
+                            hipEvent_t* ev = nullptr);
+
 // Size of the fixed device scratch of lddmm_shoot_grad_noalloc, and its device
 // address on `device` (looked up on the first call for that device, with the
 // device current; the same address afterwards).

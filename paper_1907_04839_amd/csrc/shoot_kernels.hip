@@ -327,12 +327,15 @@ __device__ __forceinline__ AdjState load_adj_state(const AdjArgs& A, int i) {
 }
 
 // Landmark i of this lane (own: it has one); part: index of the wave's H0 partial.
-// The whole wave calls it.
+// The whole wave calls it.  v becomes the state after the step (or stage); returns
+// the record written.
 template <typename R, bool RKS>
-__device__ __forceinline__ void fwd_finish(const FwdArgs& A, int i, bool own, int part, int lane,
-                                           FwdState v, const double hp[3], const double hqs[3]) {
+__device__ __forceinline__ Rec<R> fwd_finish(const FwdArgs& A, int i, bool own, int part, int lane,
+                                             FwdState& v, const double hp[3],
+                                             const double hqs[3]) {
   const int n = A.n;
   double h0 = 0.0;
+  Rec<R> out{};
   if (own) {
     if (A.hp0) {
       for (int c = 0; c < 3; ++c) A.hp0[c * n + i] = hp[c];
@@ -361,14 +364,15 @@ __device__ __forceinline__ void fwd_finish(const FwdArgs& A, int i, bool own, in
         const double w = A.rk == 1 ? 1.0 : 2.0, cs = A.rk == 3 ? A.sc.dt : 0.5 * A.sc.dt;
         double y[6];
         for (int c = 0; c < 3; ++c) {
-          A.rk_acc[c * n + i] = A.rk == 1 ? hp[c] : v.acc[c] + w * hp[c];
-          A.rk_acc[(3 + c) * n + i] = A.rk == 1 ? -hq[c] : v.acc[3 + c] + w * -hq[c];
+          v.acc[c] = A.rk == 1 ? hp[c] : v.acc[c] + w * hp[c];
+          v.acc[3 + c] = A.rk == 1 ? -hq[c] : v.acc[3 + c] + w * -hq[c];
+          A.rk_acc[c * n + i] = v.acc[c];
+          A.rk_acc[(3 + c) * n + i] = v.acc[3 + c];
           y[c] = v.q[c] + cs * hp[c];
           y[3 + c] = v.p[c] - cs * hq[c];
         }
         const double k = A.sc.k;
-        static_cast<Rec<R>*>(A.rec_t1)[i] =
-            make_rec<R>(k * y[0], k * y[1], k * y[2], y[3], y[4], y[5]);
+        out = make_rec<R>(k * y[0], k * y[1], k * y[2], y[3], y[4], y[5]);
       } else {
         for (int c = 0; c < 3; ++c) {
           v.q[c] = v.q[c] + A.sc.dt / 6.0 * (v.acc[c] + hp[c]);
@@ -381,21 +385,24 @@ __device__ __forceinline__ void fwd_finish(const FwdArgs& A, int i, bool own, in
       if (A.ckpt)
         for (int c = 0; c < 3; ++c) { A.ckpt[c * n + i] = v.q[c]; A.ckpt[(3 + c) * n + i] = v.p[c]; }
       const double k = A.sc.k;
-      static_cast<Rec<R>*>(A.rec_t1)[i] =
-          make_rec<R>(k * v.q[0], k * v.q[1], k * v.q[2], v.p[0], v.p[1], v.p[2]);
+      out = make_rec<R>(k * v.q[0], k * v.q[1], k * v.q[2], v.p[0], v.p[1], v.p[2]);
     }
+    static_cast<Rec<R>*>(A.rec_t1)[i] = out;
   }
   if (A.h0_part) {          // whole wave takes part: fixed butterfly order
     for (int off = 32; off > 0; off >>= 1) h0 += __shfl_xor(h0, off, 64);
     if (lane == 0) A.h0_part[part] = h0;
   }
+  return out;
 }
 
-// sa = A1 / kappa - A2 and sb = B of landmark i.
+// sa = A1 / kappa - A2 and sb = B of landmark i.  v becomes the adjoint after the
+// step (or stage); returns the record written.
 template <typename R, bool RKS>
-__device__ __forceinline__ void adj_finish(const AdjArgs& A, int i, AdjState v, const double sa[3],
-                                           const double sb[3]) {
+__device__ __forceinline__ Rec<R> adj_finish(const AdjArgs& A, int i, AdjState& v,
+                                             const double sa[3], const double sb[3]) {
   const int n = A.n;
+  Rec<R> out;
   if constexpr (!RKS) {
     for (int c = 0; c < 3; ++c) {
       const double Ac = A.sc.adj_a * sa[c];
@@ -404,8 +411,7 @@ __device__ __forceinline__ void adj_finish(const AdjArgs& A, int i, AdjState v, 
     }
     for (int c = 0; c < 3; ++c) { A.ad[c * n + i] = v.a[c]; A.ad[(3 + c) * n + i] = v.b[c]; }
     const double bs = A.sc.bscale;
-    static_cast<Rec<R>*>(A.arec_next)[i] =
-        make_rec<R>(v.a[0], v.a[1], v.a[2], bs * v.b[0], bs * v.b[1], bs * v.b[2]);
+    out = make_rec<R>(v.a[0], v.a[1], v.a[2], bs * v.b[0], bs * v.b[1], bs * v.b[2]);
   } else {
     // Runge-Kutta stage rk (4 down to 1): w = J(Y_rk)^T u from the pair sums;
     // lambda' + the w so far accumulates in rk_lam, and the next stage's
@@ -426,7 +432,7 @@ __device__ __forceinline__ void adj_finish(const AdjArgs& A, int i, AdjState v, 
       u[3 + c] = cl * v.b[c] + cw * wb;
     }
     if (A.rk > 1) {
-      for (int c = 0; c < 6; ++c) A.rk_lam[c * n + i] = lam[c];
+      for (int c = 0; c < 6; ++c) A.rk_lam[c * n + i] = v.lam[c] = lam[c];
     } else {
       for (int c = 0; c < 3; ++c) {
         v.a[c] = lam[c];
@@ -437,18 +443,19 @@ __device__ __forceinline__ void adj_finish(const AdjArgs& A, int i, AdjState v, 
         u[3 + c] = dt / 6.0 * v.b[c];
       }
     }
-    static_cast<Rec<R>*>(A.arec_next)[i] =
-        make_rec<R>(u[0], u[1], u[2], bs * u[3], bs * u[4], bs * u[5]);
+    out = make_rec<R>(u[0], u[1], u[2], bs * u[3], bs * u[4], bs * u[5]);
   }
+  static_cast<Rec<R>*>(A.arec_next)[i] = out;
   if (A.grad)
     for (int c = 0; c < 3; ++c) A.grad[3 * i + c] = v.b[c] + v.hp0[c];
   if (A.grad_q0)
     for (int c = 0; c < 3; ++c) A.grad_q0[3 * i + c] = v.a[c] + v.hq0[c];
+  return out;
 }
 
 // The same for the lane's landmark of i-block ib from the nine sums A1, A2, B.
 template <typename R, bool RKS>
-__device__ __forceinline__ void adj_finish9(const AdjArgs& A, int ib, int lane, const AdjState& v,
+__device__ __forceinline__ void adj_finish9(const AdjArgs& A, int ib, int lane, AdjState& v,
                                             const double s[9]) {
   const int i = ib * 64 + lane;
   if (i >= A.n) return;
@@ -653,6 +660,62 @@ __device__ __forceinline__ int row_at(int k) {
   return (k / M) * row_pad<D, M> + (k % M) * 2 * D;
 }
 
+// One pair's terms of landmark i's sums, added to h; x: q_i, p_i; y: a_i, b^_i.
+// Forward: h = {Hp, Hq's sums} (D components each).
+template <typename R, int D>
+__device__ __forceinline__ void fwd_term(const R* x, Vec3<R> q, Vec3<R> p, R* h) {
+  R d[3];
+  R r2 = (R)0, s = (R)0;
+#pragma unroll
+  for (int c = 0; c < D; ++c) {
+    d[c] = x[c] - q[c];
+    r2 = c == 0 ? d[c] * d[c] : fma(d[c], d[c], r2);
+  }
+  const R g = ex2n(r2);
+#pragma unroll
+  for (int c = 0; c < D; ++c) s = c == 0 ? x[3 + c] * p[c] : fma(x[3 + c], p[c], s);
+  const R gs = g * s;
+#pragma unroll
+  for (int c = 0; c < D; ++c) h[c] = fma(g, p[c], h[c]);
+#pragma unroll
+  for (int c = 0; c < D; ++c) h[D + c] = fma(gs, d[c], h[D + c]);
+}
+
+// Adjoint: h = {A1 / kappa - A2, B}; pi . pj = p_i . p_j / kappa (either side scaled).
+template <typename R, int D>
+__device__ __forceinline__ void adj_term(const R* x, const R* y, const R* pi, Vec3<R> q, Vec3<R> p,
+                                         Vec3<R> pj, Vec3<R> a, Vec3<R> b, R* h) {
+  R d[3], ex[3], w[3];
+  R r2 = (R)0, s = (R)0, e = (R)0, v = (R)0;
+#pragma unroll
+  for (int c = 0; c < D; ++c) {
+    d[c] = x[c] - q[c];
+    r2 = c == 0 ? d[c] * d[c] : fma(d[c], d[c], r2);
+  }
+  const R g = ex2n(r2);
+#pragma unroll
+  for (int c = 0; c < D; ++c) s = c == 0 ? pi[c] * pj[c] : fma(pi[c], pj[c], s);
+  const R gs = g * s;
+#pragma unroll
+  for (int c = 0; c < D; ++c) {
+    ex[c] = y[3 + c] - b[c];
+    e = c == 0 ? d[c] * ex[c] : fma(d[c], ex[c], e);
+  }
+#pragma unroll
+  for (int c = 0; c < D; ++c) w[c] = fma(e, p[c], a[c]);
+#pragma unroll
+  for (int c = 0; c < D; ++c) v = c == 0 ? y[c] * p[c] : fma(y[c], p[c], v);
+#pragma unroll
+  for (int c = 0; c < D; ++c) v = fma(x[3 + c], w[c], v);
+  const R gv = g * v;
+#pragma unroll
+  for (int c = 0; c < D; ++c) h[c] = fma(gs, ex[c], h[c]);
+#pragma unroll
+  for (int c = 0; c < D; ++c) h[c] = fma(-gv, d[c], h[c]);
+#pragma unroll
+  for (int c = 0; c < D; ++c) h[D + c] = fma(g, w[c], h[D + c]);
+}
+
 // Sums of one wave: rows i0 .. i0 + M - 1 over the tiles t = t0, t0 + JG, ... < t1.
 // ADJ: h[m] = {A1 / kappa - A2 (D components), B (D)}, else {Hp (D), Hq's sums (D)}.
 template <typename R, bool ADJ, int D, int M>
@@ -705,45 +768,8 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
     if constexpr (ADJ) ps = p * inv_kappa;
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      R d[3];
-      R r2 = (R)0;
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        d[c] = xi[m][c] - q[c];
-        r2 = c == 0 ? d[c] * d[c] : fma(d[c], d[c], r2);
-      }
-      const R g = ex2n(r2);
-      R s = xi[m][3] * ps[0];
-#pragma unroll
-      for (int c = 1; c < D; ++c) s = fma(xi[m][3 + c], ps[c], s);
-      const R gs = g * s;
-      if constexpr (!ADJ) {
-#pragma unroll
-        for (int c = 0; c < D; ++c) h[2 * D * m + c] = fma(g, p[c], h[2 * D * m + c]);
-#pragma unroll
-        for (int c = 0; c < D; ++c) h[2 * D * m + D + c] = fma(gs, d[c], h[2 * D * m + D + c]);
-      } else {
-        R ex[3], w[3];
-        R e = (R)0, v = (R)0;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          ex[c] = yi[m][3 + c] - b[c];
-          e = c == 0 ? d[c] * ex[c] : fma(d[c], ex[c], e);
-        }
-#pragma unroll
-        for (int c = 0; c < D; ++c) w[c] = fma(e, p[c], a[c]);
-#pragma unroll
-        for (int c = 0; c < D; ++c) v = c == 0 ? yi[m][c] * p[c] : fma(yi[m][c], p[c], v);
-#pragma unroll
-        for (int c = 0; c < D; ++c) v = fma(xi[m][3 + c], w[c], v);
-        const R gv = g * v;
-#pragma unroll
-        for (int c = 0; c < D; ++c) h[2 * D * m + c] = fma(gs, ex[c], h[2 * D * m + c]);
-#pragma unroll
-        for (int c = 0; c < D; ++c) h[2 * D * m + c] = fma(-gv, d[c], h[2 * D * m + c]);
-#pragma unroll
-        for (int c = 0; c < D; ++c) h[2 * D * m + D + c] = fma(g, w[c], h[2 * D * m + D + c]);
-      }
+      if constexpr (ADJ) adj_term<R, D>(xi[m], yi[m], &xi[m][3], q, p, ps, a, b, h + 2 * D * m);
+      else fwd_term<R, D>(xi[m], q, p, h + 2 * D * m);
     }
   }
 }
@@ -849,6 +875,170 @@ __global__ __launch_bounds__(64 * kRowWaves<R>) void k_adj_rows(AdjArgs A) {
   __shared__ R red[kRowWaves<R> * (row_pad<D, M> / 4) * 64];
   __shared__ double fin[kRowGroups * row_pad<D, M>];
   adj_rows<R, RKS, D, M>(A, blockIdx.x, red, fin);
+}
+
+// ---------------------------------------------------------------------------
+// chain kernels: all steps of a few landmarks in one launch
+// ---------------------------------------------------------------------------
+// Up to 64 landmarks a step's pair sums take a microsecond on one CU, less than the
+// launch that a step of the row kernels is.  One workgroup takes all steps:
+// records and sums stay in LDS, the FP64 state in the registers of the wave whose
+// lanes own the landmarks, and a step is three barriers.  Every wave holds all
+// landmarks i, one per lane, and takes every eighth j, whose record is an LDS
+// broadcast.  Records, state and checkpoints are stored to memory for the adjoint
+// and later launches, but no store is read back: the barriers wait for the LDS
+// alone.
+// What bounds them: barriers and LDS latency (1.2 us per step at n = 16), then the
+// pairs of one CU.  A loss+gradient evaluation of 20 Euler steps took (us, row
+// kernels -> chain): FP64 n = 16 157 -> 69, 64 160 -> 121; FP32 143 -> 56, 146 ->
+// 81; beyond 64, two landmarks per lane of the wave: FP64 n = 80 162 -> 231, FP32 96
+// 144 -> 130, 128 144 -> 157.  With 4 waves FP32 n = 64 takes 109, with 16 the same
+// 84 (FP64 spills).
+// Barrier for data in LDS (__syncthreads would wait for the stores to memory).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+constexpr int kChainWaves = 8;
+
+template <typename R>
+struct alignas(16) LdsRec { R v[sizeof(R) == 8 ? 6 : 8]; };   // q (p), p; or a, b^
+
+template <typename R>
+__device__ __forceinline__ void lds_put(LdsRec<R>* r, const Rec<R>& x) {
+  r->v[0] = x.x; r->v[1] = x.y; r->v[2] = x.z;
+  r->v[3] = x.px; r->v[4] = x.py; r->v[5] = x.pz;
+}
+
+// Sums over the waves, in their order: red[w][c][64] -> fin[c][64].
+template <typename R, int D>
+__device__ __forceinline__ void chain_combine(const R h[2 * D], R* red, double* fin, int w,
+                                              int lane) {
+#pragma unroll
+  for (int c = 0; c < 2 * D; ++c) red[(w * 2 * D + c) * 64 + lane] = h[c];
+  lds_barrier();
+  if (w < 2 * D) {
+    double s = (double)red[w * 64 + lane];
+    for (int v = 1; v < kChainWaves; ++v) s += (double)red[(v * 2 * D + w) * 64 + lane];
+    fin[w * 64 + lane] = s;
+  }
+  lds_barrier();
+}
+static_assert(kChainWaves >= 6, "a wave per sum");
+
+template <typename R, bool RKS, int D>
+__global__ __launch_bounds__(64 * kChainWaves) void k_fwd_chain(ChainArgs C, FwdArgs A) {
+  __shared__ LdsRec<R> X[64];
+  __shared__ R red[2 * D * 64 * kChainWaves];
+  __shared__ double fin[2 * D * 64];
+  const int i = threadIdx.x & 63, n = A.n, ic = min(i, n - 1);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  double* const hp0 = A.hp0;
+  double* const hq0 = A.hq0;
+  FwdState v{};
+  if (w == 0) {
+    A.rk = RKS ? 1 : 0;   // (no sums to load yet)
+    v = load_fwd_state<RKS>(A, i);
+    lds_put<R>(&X[i], static_cast<const Rec<R>*>(C.rec(C.t0, 0, n, sizeof(Rec<R>)))[ic]);
+  }
+  lds_barrier();
+  for (int t = C.t0; t < C.t1; ++t)
+    for (int st = 0; st < (RKS ? 4 : 1); ++st) {
+      const bool last = st == (RKS ? 3 : 0);
+      R h[2 * D], x[6];
+#pragma unroll
+      for (int c = 0; c < 2 * D; ++c) h[c] = (R)0;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) x[c] = X[ic].v[c];
+      for (int j = w; j < n; j += kChainWaves) {
+        const LdsRec<R> r = X[j];
+        fwd_term<R, D>(x, Vec3<R>{r.v[0], r.v[1], r.v[2]}, Vec3<R>{r.v[3], r.v[4], r.v[5]}, h);
+      }
+      chain_combine<R, D>(h, red, fin, w, i);
+      if (w == 0) {
+        double hp[3] = {0.0, 0.0, 0.0}, hq[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+          hp[c] = fin[c * 64 + i];
+          hq[c] = fin[(D + c) * 64 + i];
+        }
+        const bool field = C.first && t == 0 && st == 0;   // the field at (q0, p0)
+        A.rk = RKS ? st + 1 : 0;
+        A.rec_t1 = last ? C.rec(t + 1, 0, n, sizeof(Rec<R>)) : C.rec(t, st + 1, n, sizeof(Rec<R>));
+        A.hp0 = field ? hp0 : nullptr;
+        A.hq0 = field ? hq0 : nullptr;
+        A.h0_part = field ? C.h0_part : nullptr;
+        A.ckpt = last ? C.ckpt_of(t + 1, n) : nullptr;
+        const Rec<R> r = fwd_finish<R, RKS>(A, i, i < n, 0, i, v, hp, hq);
+        if (field && i > 0 && i < C.nh) C.h0_part[i] = 0.0;   // all of H0 is in partial 0
+        lds_put<R>(&X[i], r);
+      }
+      lds_barrier();
+    }
+}
+
+template <typename R, bool RKS, int D>
+__global__ __launch_bounds__(64 * kChainWaves) void k_adj_chain(ChainArgs C, AdjArgs A) {
+  __shared__ LdsRec<R> X[64], Y[64];
+  __shared__ R red[2 * D * 64 * kChainWaves];
+  __shared__ double fin[2 * D * 64];
+  constexpr int S = RKS ? 4 : 1;
+  const int i = threadIdx.x & 63, n = A.n, ic = min(i, n - 1);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  double* const grad = A.grad;
+  double* const grad_q0 = A.grad_q0;
+  void* const buf[2] = {A.arec_next, const_cast<void*>(A.arec)};   // written in turn
+  const R inv_kappa = (R)(1.0 / A.sc.kappa);
+  const auto rec = [&](int t, int st) {
+    return static_cast<const Rec<R>*>(C.rec(t, st, n, sizeof(Rec<R>)))[ic];
+  };
+  AdjState v{};
+  Rec<R> next{};   // the record of the coming stage, loaded a stage ahead
+  if (w == 0) {
+    if (C.t0 > 0) { A.grad = nullptr; A.grad_q0 = nullptr; }
+    A.rk = RKS ? 4 : 0;   // (no sums to load yet)
+    v = load_adj_state<RKS>(A, i);
+    lds_put<R>(&Y[i], static_cast<const Rec<R>*>(A.arec)[ic]);
+    next = rec(C.t1 - 1, S - 1);
+  }
+  int k = 0;
+  for (int t = C.t1 - 1; t >= C.t0; --t)
+    for (int st = S - 1; st >= 0; --st, ++k) {
+      if (w == 0) {
+        lds_put<R>(&X[i], next);
+        if (st > 0) next = rec(t, st - 1);
+        else if (t > C.t0) next = rec(t - 1, S - 1);
+      }
+      lds_barrier();
+      R h[2 * D], x[6], y[6], pi[3];
+#pragma unroll
+      for (int c = 0; c < 2 * D; ++c) h[c] = (R)0;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) { x[c] = X[ic].v[c]; y[c] = Y[ic].v[c]; }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) pi[c] = x[3 + c] * inv_kappa;
+      for (int j = w; j < n; j += kChainWaves) {
+        const LdsRec<R> r = X[j], z = Y[j];
+        const Vec3<R> p{r.v[3], r.v[4], r.v[5]};
+        adj_term<R, D>(x, y, pi, Vec3<R>{r.v[0], r.v[1], r.v[2]}, p, p,
+                       Vec3<R>{z.v[0], z.v[1], z.v[2]}, Vec3<R>{z.v[3], z.v[4], z.v[5]}, h);
+      }
+      chain_combine<R, D>(h, red, fin, w, i);
+      if (w == 0 && i < n) {
+        double sa[3] = {0.0, 0.0, 0.0}, sb[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+          sa[c] = fin[c * 64 + i];
+          sb[c] = fin[(D + c) * 64 + i];
+        }
+        const bool end = t == 0 && st == 0;
+        A.rk = RKS ? st + 1 : 0;
+        A.arec_next = buf[k & 1];
+        A.grad = end ? grad : nullptr;
+        A.grad_q0 = end ? grad_q0 : nullptr;
+        lds_put<R>(&Y[i], adj_finish<R, RKS>(A, i, v, sa, sb));
+      }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1188,7 +1378,7 @@ template <typename R, bool COMP, int SC, bool RKS>
 __global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_fwd_update(FwdArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   const int ib = blockIdx.x, lane = threadIdx.x;
-  const FwdState v = load_fwd_state<RKS>(A, ib * 64 + lane);
+  FwdState v = load_fwd_state<RKS>(A, ib * 64 + lane);
   double h[6];
   gather_partials<Acc, 6, SC>(static_cast<const Acc*>(A.partial), A.n, A.S,
                               min(ib * 64 + lane, A.n - 1), h);
@@ -1199,7 +1389,7 @@ template <typename R, bool COMP, int SC, bool RKS>
 __global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_adj_update(AdjArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   const int ib = blockIdx.x, lane = threadIdx.x;
-  const AdjState v = load_adj_state<RKS>(A, ib * 64 + lane);
+  AdjState v = load_adj_state<RKS>(A, ib * 64 + lane);
   double h[9];
   gather_partials<Acc, 9, SC>(static_cast<const Acc*>(A.partial), A.n, A.S,
                               min(ib * 64 + lane, A.n - 1), h);
@@ -1666,6 +1856,39 @@ hipError_t launch_restore(int mode, int n, const double* ckpt, double k, double*
     k_restore<double><<<blocks256(n), 256, 0, s>>>(n, ckpt, k, st, static_cast<Rec<double>*>(rec));
   else
     k_restore<float><<<blocks256(n), 256, 0, s>>>(n, ckpt, k, st, static_cast<Rec<float>*>(rec));
+  return hipGetLastError();
+}
+
+template <typename R>
+void fwd_chain_dispatch(const ChainArgs& c, const FwdArgs& a, hipStream_t s, hipEvent_t* ev) {
+  auto* k = c.spt == 4 ? (a.dim == 2 ? k_fwd_chain<R, true, 2> : k_fwd_chain<R, true, 3>)
+                       : (a.dim == 2 ? k_fwd_chain<R, false, 2> : k_fwd_chain<R, false, 3>);
+  const dim3 threads(64 * kChainWaves);
+  if (ev) hipExtLaunchKernelGGL(k, dim3(1), threads, 0, s, ev[0], ev[1], 0, c, a);
+  else k<<<1, threads, 0, s>>>(c, a);
+}
+template <typename R>
+void adj_chain_dispatch(const ChainArgs& c, const AdjArgs& a, hipStream_t s, hipEvent_t* ev) {
+  auto* k = c.spt == 4 ? (a.dim == 2 ? k_adj_chain<R, true, 2> : k_adj_chain<R, true, 3>)
+                       : (a.dim == 2 ? k_adj_chain<R, false, 2> : k_adj_chain<R, false, 3>);
+  const dim3 threads(64 * kChainWaves);
+  if (ev) hipExtLaunchKernelGGL(k, dim3(1), threads, 0, s, ev[0], ev[1], 0, c, a);
+  else k<<<1, threads, 0, s>>>(c, a);
+}
+
+hipError_t launch_fwd_chain(int mode, const ChainArgs& c, const FwdArgs& a, hipStream_t s,
+                            hipEvent_t* ev) {
+  if (a.n > kChainMax) return hipErrorInvalidValue;
+  if (mode == kFP64) fwd_chain_dispatch<double>(c, a, s, ev);
+  else fwd_chain_dispatch<float>(c, a, s, ev);
+  return hipGetLastError();
+}
+
+hipError_t launch_adj_chain(int mode, const ChainArgs& c, const AdjArgs& a, hipStream_t s,
+                            hipEvent_t* ev) {
+  if (a.n > kChainMax) return hipErrorInvalidValue;
+  if (mode == kFP64) adj_chain_dispatch<double>(c, a, s, ev);
+  else adj_chain_dispatch<float>(c, a, s, ev);
   return hipGetLastError();
 }
 
