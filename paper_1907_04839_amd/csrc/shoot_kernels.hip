@@ -740,13 +740,15 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
 #pragma unroll
   for (int k = 0; k < row_pad<D, M>; ++k) h[k] = (R)0;
   struct Tile { Vec3<R> q, p, a, b; };
-  const auto load = [&](int j) {
+  // 32-bit byte offsets from a scalar base: an address is one instruction (with the
+  // narrower mask below 2-4 % of a step, FP64 n = 2500 forward 14.1 -> 12.8 us)
+  const auto load = [&](unsigned o) {
     Tile r;
-    const GlobalPtr<Rec<R>> x = X + j;
+    const GlobalPtr<Rec<R>> x = (GlobalPtr<Rec<R>>)((GlobalPtr<char>)X + o);
     r.q = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&x->x);
     r.p = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&x->px);
     if constexpr (ADJ) {
-      const GlobalPtr<Rec<R>> y = Y + j;
+      const GlobalPtr<Rec<R>> y = (GlobalPtr<Rec<R>>)((GlobalPtr<char>)Y + o);
       r.a = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&y->x);
       r.b = *reinterpret_cast<GlobalPtr<Vec3<R>>>(&y->px);
     }
@@ -754,16 +756,21 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
   };
   // one tile ahead (the last one twice): with few waves per SIMD the loads'
   // latency shows (FP64, n = 2500: adjoint 21.6 us per step without, 19.9 with)
-  int j = t0 * 64 + lane;
-  Tile next = load(min(j, n - 1));
+  constexpr unsigned kRec = sizeof(Rec<R>);
+  const unsigned end = (unsigned)(n - 1) * kRec;
+  unsigned o = (unsigned)(t0 * 64 + lane) * kRec;
+  Tile next = load(min(o, end));
   for (int t = t0; t < t1; t += JG) {
-    const bool in = j < n;
+    const bool in = o <= end;
     const Tile cur = next;
-    j += 64 * JG;
-    next = load(min(j, n - 1));
+    o += 64 * kRec * (unsigned)JG;
+    next = load(min(o, end));
     Vec3<R> q = cur.q, p = cur.p, a = (R)0, b = (R)0;
     if constexpr (ADJ) { a = cur.a; b = cur.b; }
-    if (!in) { q = (R)0; p = (R)0; a = (R)0; b = (R)0; }   // adds an exact 0 to every sum
+    // adds an exact 0 to every sum (the adjoint would do with p and a as well, but
+    // its loop comes out slower then: 2D n = 3000 10.8 against 9.8 us per step)
+    if (!in) p = (R)0;
+    if (ADJ && !in) { q = (R)0; a = (R)0; b = (R)0; }
     Vec3<R> ps = p;
     if constexpr (ADJ) ps = p * inv_kappa;
 #pragma unroll
@@ -1372,10 +1379,10 @@ __device__ __forceinline__ void gather_partials(const Acc* __restrict__ P, int n
 
 // One wave per i-block and latency-bound: let the scheduler spend registers
 // on loads in flight rather than on occupancy.
-#define LDDMM_BATCHNCY_BOUND __attribute__((amdgpu_waves_per_eu(1, 2)))
+#define LDDMM_LATENCY_BOUND __attribute__((amdgpu_waves_per_eu(1, 2)))
 
 template <typename R, bool COMP, int SC, bool RKS>
-__global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_fwd_update(FwdArgs A) {
+__global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_fwd_update(FwdArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   const int ib = blockIdx.x, lane = threadIdx.x;
   FwdState v = load_fwd_state<RKS>(A, ib * 64 + lane);
@@ -1386,7 +1393,7 @@ __global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_fwd_update(FwdArgs 
 }
 
 template <typename R, bool COMP, int SC, bool RKS>
-__global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_adj_update(AdjArgs A) {
+__global__ __launch_bounds__(64) LDDMM_LATENCY_BOUND void k_adj_update(AdjArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   const int ib = blockIdx.x, lane = threadIdx.x;
   AdjState v = load_adj_state<RKS>(A, ib * 64 + lane);
@@ -1401,7 +1408,7 @@ __global__ __launch_bounds__(64) LDDMM_BATCHNCY_BOUND void k_adj_update(AdjArgs 
 // second memory round trip.  Wave 1 sums components 5-8 (in chunk order, as
 // above) and hands them over through LDS; wave 0 sums 0-4 and finishes.
 template <typename R, bool COMP, int SC, bool RKS>
-__global__ __launch_bounds__(128) LDDMM_BATCHNCY_BOUND void k_adj_update2(AdjArgs A) {
+__global__ __launch_bounds__(128) LDDMM_LATENCY_BOUND void k_adj_update2(AdjArgs A) {
   using Acc = typename AccOf<R, COMP>::type;
   __shared__ double red[4 * 64];
   const int ib = blockIdx.x, lane = threadIdx.x & 63;
