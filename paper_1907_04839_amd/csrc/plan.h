@@ -92,55 +92,33 @@ inline Plan make_plan(int n, int target_waves) {
 // best width depends on the kernel instance's registers and LDS and on how
 // many workgroups share a CU.  Measured per precision mode and kind of step
 // (ms per loss+gradient evaluation; widths forward/adjoint 12/12, 8/8, 16/16;
-// Euler unless marked):
+// Euler unless marked; the smaller sizes stand for the shape of a step, the row
+// kernels take those up to 5120 in FP32 and 3072 in FP64):
 //   FP32-compensated: N = 4096 1.298, 1.351, 1.451; 16384 (T = 4) 1.298,
-//     1.322, 1.585; 65536 (T = 3) 14.38, 14.78, 17.35; 800 (T = 10) 0.167,
-//     0.187, 0.163; Runge-Kutta N = 4096 (T = 10) 1.317, 1.378, 1.469
-//     -> 12/12 everywhere.  Its 16-wave workgroups, like the FP64 ones, hold
-//     72 KiB of LDS for the wave combine and were slow wherever workgroups
-//     share a CU.
+//     1.322, 1.585; 65536 (T = 3) 14.38, 14.78, 17.35; Runge-Kutta N = 4096
+//     (T = 10) 1.317, 1.378, 1.469 -> 12/12 everywhere.  Its 16-wave workgroups,
+//     like the FP64 ones, hold 72 KiB of LDS for the wave combine and were slow
+//     wherever workgroups share a CU.
 //   FP32 (16/16 first): N = 4096 1.213, 1.241, 1.296; 32768 (T = 2) 2.384,
-//     2.438, 2.446; 65536 13.93, 14.17, 14.33; 800 0.156, 0.162, 0.183
-//     -> 16/16; Runge-Kutta N = 4096 1.288, 1.269, 1.320; 800 (T = 3) 0.192,
-//     0.199, 0.227 -> 12/12, or 16/16 where a launch has at most one
-//     workgroup per CU.
+//     2.438, 2.446; 65536 13.93, 14.17, 14.33 -> 16/16; Runge-Kutta N = 4096
+//     1.288, 1.269, 1.320 -> 12/12.
 //   FP64: N = 4096 2.314, 2.415, 2.694; 16384 2.845, 2.913, 3.310; 65536
-//     33.58, 34.43, 41.39; with at most one workgroup per CU (16/16 first)
-//     N = 800 0.245, 0.261, 0.312 and 1847 0.938, 0.952, 0.994 -> 16/16 there,
-//     else 12/12; Runge-Kutta N = 4096 8/8 2.356 against 2.573 (12/12) ->
-//     unwidened unless at most one workgroup per CU (16/16: N = 800 0.286
-//     against 0.350 at 8/8).
+//     33.58, 34.43, 41.39 -> 12/12; Runge-Kutta N = 4096 8/8 2.356 against 2.573
+//     (12/12) -> unwidened.
 // Widths 10 and 14 leave the four SIMDs unevenly loaded (measured slower).
 // The sum order within a workgroup follows the width, so results change at
 // rounding level.
 inline void widen_plan(Plan& p, int mode, bool rk) {
-  constexpr int kCUs = 256;   // MI355X
   if (p.W != 8) return;
   if (p.S != 8 && p.S != 4 && p.S != 3 && p.S != 2) return;
   // make_plan also gives 8 x 2 plans at N = 144-271, where 12 or 16 waves
   // would leave fewer than 8 (or no) j per wave: the 8 x 2 widths were
   // measured at N = 65536 only, so they apply where every wave keeps >= 16 j.
   if (p.S == 2 && (p.chunk + 15) / 16 < 16) return;
-  const bool one_per_cu = p.nb * p.S <= kCUs;
-  int wf = 8, wa = 8;
-  if (rk) {
-    if (mode == kFP32Comp) { wf = wa = 12; }
-    else if (mode == kFP32) { wf = wa = one_per_cu ? 16 : 12; }
-    else if (mode == kFP64) {
-      if (!one_per_cu) return;   // 12 or 16 waves measured slower there
-      wf = wa = 16;
-    }
-  } else if (mode == kFP32Comp) {
-    wf = wa = 12;
-  } else if (mode == kFP32) {
-    wf = wa = 16;
-  } else if (mode == kFP64) {
-    wf = wa = one_per_cu ? 16 : 12;
-  }
-  p.W = wf;
-  p.wchunk = (p.chunk + wf - 1) / wf;
-  p.Wa = wa;
-  p.wchunk_a = (p.chunk + wa - 1) / wa;
+  if (rk && mode == kFP64) return;
+  const int w = mode == kFP32 && !rk ? 16 : 12;
+  p.W = p.Wa = w;
+  p.wchunk = p.wchunk_a = (p.chunk + w - 1) / w;
 }
 
 // The row kernels take the sizes where a step is bound by its launches rather
@@ -148,17 +126,21 @@ inline void widen_plan(Plan& p, int mode, bool rk) {
 // per loss+gradient evaluation (us, T = 20; split kernels against row kernels):
 //   FP32-compensated: n = 200 293 -> 157; 1000 298 -> 187; 1847 339 -> 256;
 //     2500 494 -> 353; 3001 550 -> 412; 4096 658 -> 606; 5000 994 -> 907; 6000
-//     1133 -> 1207, where the split kernels' loops are the faster ones.
+//     1133 -> 1150, 8192 1819 -> 1913, 16384 6211 -> 6937, where the split kernels'
+//     loops, which have no loads and masks per pair, are the faster ones.
 //   FP64: n = 64 222 -> 140 (the split plan's one launch per step runs one
 //     workgroup); 500 375 -> 176; 1000 354 -> 233; 1847 475 -> 418; 2500 809 ->
 //     722; 3001 933 -> 839; 4096 1188 -> 1340.
 // m is chosen for the fullest CU's work, ceil(groups / 256) (m + 1): m rows and
 // about one row's time for a wave's loads, the larger m of equals.  At n = 1300
 // m = 3, 4, 5 took 219, 234, 260 us, at n = 2500 390, 372, 353; FP64 at n = 2500
-// (adjoint step) 25.7 us for m = 2 and 21.8 for m = 4.  One workgroup per CU gets 8 waves; with up to two,
-// both are merged into one, whose i-groups share their j records in the
-// CU's cache (n = 1847: 266 -> 256 us; FP64 475 -> 418).  FP64 waves hold twice
-// the registers: 8 per workgroup at most.
+// (adjoint step) 25.7 us for m = 2 and 21.8 for m = 4.  One workgroup per CU gets
+// 8 waves; with up to two, both are merged into one, whose i-groups share their j
+// records in the CU's cache (n = 1847: 266 -> 256 us; FP64 475 -> 418).  FP64 waves
+// hold twice the registers: 8 per workgroup at most.  In FP32 workgroups of four
+// waves are the better ones from n = 3073 on, where several share a CU and a wave
+// still has 12 tiles or more (n = 4096 624 -> 605, 5000 855 -> 833; but 3001 410 ->
+// 442, 2500 341 -> 387).
 inline RowPlan row_plan(int n, int mode) {
   constexpr int kCUs = 256;   // MI355X
   const bool f64 = mode == kFP64;
@@ -176,7 +158,7 @@ inline RowPlan row_plan(int n, int mode) {
   }
   const int g = groups(r.m), tiles = (n + 63) / 64;
   r.ig = g > kCUs && g <= 2 * kCUs ? 2 : 1;
-  r.jg = f64 && g > kCUs ? 4 : 8;
+  r.jg = (f64 ? g > kCUs : n > 3072) ? 4 : 8;
   if (r.jg > tiles) r.jg = tiles;
   r.groups = groups(r.m * r.ig);
   return r;
@@ -214,8 +196,9 @@ inline RowPlan batch_plan(int n) {
 // The most workgroups that a job of at most max_n landmarks has.
 inline int batch_groups(int max_n) {
   int g = batch_plan(max_n).groups;
-  for (const int n : {8191, 16383})
-    if (n < max_n && batch_plan(n).groups > g) g = batch_plan(n).groups;
+  const int last[2] = {8191, 16383};   // of the plans with more i-groups after them
+  for (int k = 0; k < 2; ++k)
+    if (last[k] < max_n && batch_plan(last[k]).groups > g) g = batch_plan(last[k]).groups;
   return g;
 }
 
