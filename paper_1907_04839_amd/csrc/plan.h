@@ -173,10 +173,10 @@ constexpr int kChainMax = 64;
 // eight jobs of 500 to 8000 landmarks, one of 2000, four of 1500, eight of 400):
 //   12-wave workgroups of 64 landmarks     46.7  11.6  11.7  4.88
 //   8 waves, m = 5                         43.6   4.22  8.36 4.93
-//   4 waves, m = 5                         37.2   4.25  6.73 3.88
-//   4 waves, m = 4                         39.4   3.86  6.44 3.78   (taken)
 //   2 waves, m = 5                         41.6   5.84  7.18 4.00
-// and FP64 (T = 10) 38.1, 8.90, 9.05 -> 22.8, 1.78, 3.41 (first three sets).
+//   4 waves, m = 5                         36.0   4.13  6.26 3.69
+//   4 waves, m = 4                         37.1   3.85  6.21 3.49   (taken)
+// and FP64 (T = 10) 38.1, 8.90, 9.05 -> 22.2, 1.77, 3.41 (first three sets).
 // The waves share the j tiles (jg = 4), which a job alone on the chip needs (one of
 // 2000 with jg = 1: 9.5 ms); from n = 8192 on there are rows enough to fill it
 // with two and then four i-groups, whose waves share their j records.
