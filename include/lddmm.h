@@ -66,8 +66,10 @@ typedef enum {
 /* Precision of the O(N^2) pair sums.  State, Euler updates, H, the loss and
  * the optimiser are FP64 in every mode. */
 typedef enum {
-  LDDMM_FP32 = 0,          /* FP32 pair terms, one running FP32 sum per wave */
-  LDDMM_FP32_COMP = 1,     /* FP32 pair terms, FP32 sums of 72 pairs folded into FP64 */
+  LDDMM_FP32 = 0,          /* FP32 pair terms, one running FP32 sum per wave (up to
+                              5120 landmarks, in a server and for carried points
+                              the same sums as LDDMM_FP32_COMP) */
+  LDDMM_FP32_COMP = 1,     /* FP32 pair terms, FP32 sums of <= 72 pairs folded into FP64 */
   LDDMM_FP64 = 2           /* FP64 throughout */
 } lddmm_precision;
 

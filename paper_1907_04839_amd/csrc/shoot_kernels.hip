@@ -7,26 +7,31 @@
 // materialising the N x N kernel matrix (Sec. 2.5); this file keeps that idea
 // and re-plans it for wave64 hardware:
 //
-//  * Lane l of a wave owns landmark i = 64 ib + l and keeps its data and its
-//    running sums in VGPRs.  The j landmarks are wave-uniform, so their
-//    records arrive through scalar loads into SGPRs and every VALU
-//    instruction of the pair term reads at most one SGPR operand; there is no
-//    LDS traffic and no barrier inside the j loop.
+//  * Large problems (split kernels): lane l of a wave owns landmark i = 64 ib + l
+//    and keeps its data and its running sums in VGPRs.  The j landmarks are
+//    wave-uniform, so their records arrive through scalar loads into SGPRs and
+//    every VALU instruction of the pair term reads at most one SGPR operand;
+//    there is no LDS traffic and no barrier inside the j loop.
+//  * A few thousand landmarks (row kernels, and the batched kernels of the
+//    server): lanes own the j, a wave's few rows i are uniform, a workgroup sees
+//    every j of its rows and ends the step in the same launch.  Up to 64
+//    landmarks (chain kernels) one launch takes all steps.
 //  * Coordinates are stored pre-scaled by k = sqrt(log2(e) / (2 sigma^2)), so
 //    g_ij = exp2(-|k q_i - k q_j|^2) is one v_exp_f32 with a negate modifier.
-//    A forward pair costs 16 VALU + 1 exp, an adjoint pair 37 VALU + 1 exp.
-//  * The j range is split over the W waves of a workgroup and, when one
-//    workgroup per i-block would not fill the chip, over S workgroups.
+//    A forward pair costs 16 VALU + 1 exp, an adjoint pair 35 to 37 VALU + 1 exp.
+//  * The split kernels' j range is cut over the W waves of a workgroup and, when
+//    one workgroup per i-block would not fill the chip, over S workgroups.
 //    Partials are combined in a fixed order (waves through LDS, workgroups
 //    through a [S][C][N] buffer): no float atomics, so results are
 //    bit-reproducible and depend only on N, never on what else is running.
-//  * Precision modes: FP32 with one running FP32 sum per wave ("naive");
-//    FP32 with per-72-pair FP32 tile sums folded into FP64 ("compensated");
-//    or everything in FP64 (with an own 2^x).  The live state (q, p, a, b),
-//    the Euler updates, the Hamiltonian and the loss are FP64 in every mode.
+//  * Precision modes: FP32 with one running FP32 sum per wave ("naive", in the
+//    split kernels); FP32 with FP32 sums of at most 72 pairs folded into FP64
+//    ("compensated", and both FP32 modes of the other kernels); or everything in
+//    FP64 (with an own 2^x).  The live state (q, p, a, b), the Euler updates, the
+//    Hamiltonian and the loss are FP64 in every mode.
 //  * Planar problems instantiate the same loops without the z terms, and
-//    the flow of arbitrary points (eq. 4) carries each point, one per lane,
-//    through all steps of the stored trajectory in a single launch.
+//    the flow of arbitrary points (eq. 4) carries its points through all steps of
+//    the stored trajectory in a single launch.
 //  * Classical Runge-Kutta steps (an option beside the paper's Euler steps)
 //    reuse the pair loops stage by stage; separate compile-time instances
 //    (RKS) hold the stage bookkeeping so that the Euler kernels carry none.
