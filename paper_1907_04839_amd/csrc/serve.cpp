@@ -523,7 +523,10 @@ lddmm_status lddmm_server_create(const lddmm_server_config* cfg, lddmm_server** 
   s->cfg = *cfg;
   s->t0 = Clock::now();
   const int M = cfg->max_slots;
-  s->capacity = M * batch_groups(cfg->max_n);
+  // items of the most that can run at once: M jobs of max_n landmarks, or as many
+  // landmarks as the arena holds (a landmark takes more than 400 bytes of it)
+  const size_t in_arena = M + cfg->hbm_budget_bytes / (400 * kBatchRows);
+  s->capacity = (int)std::min(in_arena, (size_t)M * batch_groups(cfg->max_n));
   s->tab.assign(M, BatchJob{});
   s->ltab.assign(M, LbfgsJob{});
   s->slot_job.assign(M, nullptr);
