@@ -168,20 +168,33 @@ inline RowPlan row_plan(int n, int mode) {
 // comment has the figures on both sides of the line.
 constexpr int kChainMax = 64;
 
-// Row plans of the batched kernels: four waves of four rows per workgroup.
-// Measured on the solves of a server (ms, FP32-compensated, T = 40, 4 iterations;
-// eight jobs of 500 to 8000 landmarks, one of 2000, four of 1500, eight of 400):
-//   12-wave workgroups of 64 landmarks     46.7  11.6  11.7  4.88
-//   8 waves, m = 5                         43.6   4.22  8.36 4.93
-//   2 waves, m = 5                         41.6   5.84  7.18 4.00
-//   4 waves, m = 5                         36.0   4.13  6.26 3.69
-//   4 waves, m = 4                         37.1   3.85  6.21 3.49   (taken)
-// and FP64 (T = 10) 38.1, 8.90, 9.05 -> 22.2, 1.77, 3.41 (first three sets).
+// Kernels of a server's batches.  Row items are short, so a few jobs of uneven size,
+// or one alone, still fill the chip evenly; i-blocks of 64 landmarks run the split
+// kernels' faster loops (165 cycles per forward + adjoint pair against about 200)
+// but need many workgroups of them: one of n = 8000 keeps a CU for 46 us (forward),
+// more than the CU's share of such a batch.  How many jobs share the chip is what a
+// server's configuration says: rows up to max_slots ceil(max_n / 64) = 1024.  Solves, ms
+// (FP32-compensated, T = 40, 4 iterations; blocks | rows):
+//   8 slots: 500 to 8000 46.9 | 35.1, eight of 8000 133 | 138; 4 of 1500 11.7 | 6.4;
+//   1 of 2000 11.5 | 4.1; 32 slots: 500 to 8000 96 | 111; FP64 (T = 10) 500 to 8000
+//   38.1 | 21.3, eight of 8000 92 | 87.
+inline bool batch_blocks(int max_slots, int max_n) {
+  return (long long)max_slots * ((max_n + 63) / 64) > 1024;
+}
+
+// Row plans of the batched kernels: four waves of five rows per workgroup.
+// Measured as above (ms; eight jobs of 500 to 8000 landmarks, one of 2000, four of
+// 1500; 8-wave items before the loops' later steps):
+//   8 waves, m = 5                         43.6   4.22  8.36
+//   2 waves, m = 5                         41.6   5.84  7.18
+//   4 waves, m = 4, 5, 6, 8                36.6, 34.4, 39.7, 41.2;  3.82, 4.12, 4.76,
+//                                          4.82;  6.12, 6.38, 6.80, 7.27
+// and FP64 (T = 10) blocks 38.1, 8.90, 9.05, rows 22.2, 1.77, 3.41 (m = 4).
 // The waves share the j tiles (jg = 4), which a job alone on the chip needs (one of
 // 2000 with jg = 1: 9.5 ms); from n = 8192 on there are rows enough to fill it
 // with two and then four i-groups, whose waves share their j records.
 constexpr int kBatchWaves = 4;
-constexpr int kBatchRows = 4;
+constexpr int kBatchRows = 5;
 constexpr int kBatchGrid = 2048;   // workgroups of a launch, at most
 
 inline RowPlan batch_plan(int n) {

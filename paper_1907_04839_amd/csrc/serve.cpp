@@ -8,7 +8,7 @@
 // and one optimiser step per round, as one replay of a captured hipGraph:
 // batched stage, T forward pair-sum launches, batched loss, T adjoint
 // launches, batched L-BFGS step.  Each pair-sum launch covers every
-// (job, group of rows) item of its kind (once planar jobs have come,
+// (job, group of rows or i-block) item of its kind (once planar jobs have come,
 // each step has a launch for the 3D items and one for the planar items,
 // which leave the z terms out), so small jobs share the chip instead of
 // leaving it idle.  Jobs join at the next round after admission and leave
@@ -102,7 +102,8 @@ T* at(void* base, size_t off) { return reinterpret_cast<T*>(static_cast<char*>(b
 
 struct lddmm_server {
   lddmm_server_config cfg{};
-  int capacity = 0;                 // pair-kernel workgroups per launch (max items)
+  int capacity = 0;                 // items at most
+  bool blocks = false;              // items are i-blocks, not groups of rows
   Clock::time_point t0;
 
   void* arena_base = nullptr;
@@ -221,7 +222,9 @@ bool admit(lddmm_server* s, ServerJob* j, int k) {
   BatchJob b{};
   b.active = 1;
   b.n = n;
+  b.nb = (n + 63) / 64;
   b.row = batch_plan(n);
+  b.nh = s->blocks ? b.nb : b.row.groups;
   b.lambda = j->p.lambda;
   b.sc = sc;
   b.q0 = q0;
@@ -294,7 +297,7 @@ bool upload_tables(lddmm_server* s, int parity) {
                      [&](int a, int b) { return s->tab[a].n > s->tab[b].n; });
     const int first = ni;
     for (int k : order)
-      for (int g = 0; g < s->tab[k].row.groups; ++g) s->h_items[parity][ni++] = make_int2(k, g);
+      for (int g = 0; g < s->tab[k].nh; ++g) s->h_items[parity][ni++] = make_int2(k, g);
     s->h_nitems[parity][dim == 3 ? 0 : 1] = ni - first;
     if (ni > first) s->dims_seen |= dim == 3 ? 1 : 2;
   }
@@ -328,14 +331,14 @@ bool build_graph(lddmm_server* s) {
     for (int k = s0; k <= s1 && e == hipSuccess; ++k)
       for (int d : {3, 2})
         if (e == hipSuccess && (dims & (d == 3 ? 1 : 2)))
-          e = launch_fwd_batch(mode, d, s->d_jobs, s->d_items, s->d_nitems, s->capacity, t, k,
+          e = launch_fwd_batch(mode, d, s->blocks, s->d_jobs, s->d_items, s->d_nitems, s->capacity, t, k,
                                st);
   if (e == hipSuccess) e = launch_loss_batch(mode, s->d_jobs, M, st);
   for (int t = T - 1; t >= 0 && e == hipSuccess; --t)
     for (int k = s1; k >= s0 && e == hipSuccess; --k)
       for (int d : {3, 2})
         if (e == hipSuccess && (dims & (d == 3 ? 1 : 2)))
-          e = launch_adj_batch(mode, d, s->d_jobs, s->d_items, s->d_nitems, s->capacity, t, k,
+          e = launch_adj_batch(mode, d, s->blocks, s->d_jobs, s->d_items, s->d_nitems, s->capacity, t, k,
                                T, st);
   if (e == hipSuccess) e = launch_lbfgs_step_batch(s->d_ljobs, M, st);
   if (e == hipSuccess) e = launch_gather_done(s->d_ljobs, M, s->d_done, st);
@@ -523,10 +526,9 @@ lddmm_status lddmm_server_create(const lddmm_server_config* cfg, lddmm_server** 
   s->cfg = *cfg;
   s->t0 = Clock::now();
   const int M = cfg->max_slots;
-  // items of the most that can run at once: M jobs of max_n landmarks, or as many
-  // landmarks as the arena holds (a landmark takes more than 400 bytes of it)
-  const size_t in_arena = M + cfg->hbm_budget_bytes / (400 * kBatchRows);
-  s->capacity = (int)std::min(in_arena, (size_t)M * batch_groups(cfg->max_n));
+  // items of the most that can run at once: M jobs of max_n landmarks
+  s->blocks = batch_blocks(M, cfg->max_n);
+  s->capacity = M * (s->blocks ? (cfg->max_n + 63) / 64 : batch_groups(cfg->max_n));
   s->tab.assign(M, BatchJob{});
   s->ltab.assign(M, LbfgsJob{});
   s->slot_job.assign(M, nullptr);

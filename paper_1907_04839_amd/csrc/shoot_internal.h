@@ -149,13 +149,14 @@ hipError_t launch_forward_out(int n, int nb, const double* st, const double* cen
 
 // One registration of a batched launch, as the batched kernels see it.  All
 // jobs of a batch share T, the precision and the kind of step; planar and 3D
-// jobs have pair kernels of their own.  A job's decomposition (batch_plan) follows
-// from its n alone, so its results do not depend on which other jobs share the
-// launch.
+// jobs have pair kernels of their own.  A job's decomposition follows from its n
+// and the server's configuration alone (batch_blocks, batch_plan), so its results
+// do not depend on which other jobs share the launch.
 struct BatchJob {
   int active;               // the slot holds a job
-  int n;
+  int n, nb;
   RowPlan row;
+  int nh;                   // partial sums of H0 in h0p: one per item
   double lambda;
   Scales sc;
   const double* q0;         // [n][3] template
@@ -170,20 +171,28 @@ struct BatchJob {
   double *rk_acc, *rk_lam;  // [6][n] each, Runge-Kutta steps only
 };
 
+// Waves per workgroup of the block kernels of a batch.  On the 48-job serving
+// stream (FP32-compensated, Euler steps) 12-wave workgroups gave 15.7 solves/s
+// against 14.9 for 8-wave and 13.8 for 16-wave ones: two 12-wave workgroups
+// fill the 24 wave slots per CU that the adjoint's registers leave.  FP32,
+// FP64 and Runge-Kutta stage instances keep 8 (their registers differ; 12 was
+// measured only in the FP32-compensated Euler case).
+constexpr int batch_waves(bool compensated, bool rk) { return compensated && !rk ? 12 : 8; }
+
 // Launch shapes of a batch of at most max_slots jobs with n <= max_n:
-// stage (max_n/256, max_slots), pair kernels at most kBatchGrid workgroups that
-// share the items ((job, workgroup of its row plan), at most `capacity`), loss
-// max_slots.  items holds nitems[0] items of 3D
+// stage (max_n/256, max_slots), loss max_slots.  Pair kernels: `blocks`, capacity
+// workgroups, one per (job, i-block) item, those beyond the items exit; else at
+// most kBatchGrid workgroups that share the items (job, workgroup of its row plan).  items holds nitems[0] items of 3D
 // jobs followed by nitems[1] items of planar jobs; the pair launch for dim 3
 // (or 2) takes its group.
 hipError_t launch_stage_batch(int mode, const BatchJob* jobs, int max_slots, int max_n,
                               hipStream_t s);
 // stage: 0 for an Euler step, else the Runge-Kutta stage (1..4) of step t;
 // every job of the batch takes steps of the same kind.
-hipError_t launch_fwd_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
+hipError_t launch_fwd_batch(int mode, int dim, bool blocks, const BatchJob* jobs, const int2* items,
                             const int* nitems, int capacity, int t, int stage, hipStream_t s);
 hipError_t launch_loss_batch(int mode, const BatchJob* jobs, int max_slots, hipStream_t s);
-hipError_t launch_adj_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
+hipError_t launch_adj_batch(int mode, int dim, bool blocks, const BatchJob* jobs, const int2* items,
                             const int* nitems, int capacity, int t, int stage, int T,
                             hipStream_t s);
 

@@ -784,10 +784,17 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
     next = load(min(o, end));
     Vec3<R> q = cur.q, p = cur.p, a = (R)0, b = (R)0;
     if constexpr (ADJ) { a = cur.a; b = cur.b; }
-    // adds an exact 0 to every sum (the adjoint would do with p and a as well, but
-    // its loop comes out slower then: 2D n = 3000 10.8 against 9.8 us per step)
-    if (!in) p = (R)0;
-    if (ADJ && !in) { q = (R)0; a = (R)0; b = (R)0; }
+    // Lanes beyond n add an exact 0 to every sum with p_j = a_j = 0.  In the batched
+    // kernels a branch keeps that to the ragged tile (eight jobs of 500 to 8000: 36.0
+    // -> 34.4 ms); in the others the adjoint's loop comes out slower then (n = 2500
+    // 9.7 -> 11.7 us per step), and slower too when it does not zero q and b (2D n = 3000
+    // 9.8 -> 10.8).
+    if constexpr (BATCH) {
+      if (t * 64 + 64 > n && !in) { p = (R)0; a = (R)0; }
+    } else {
+      if (!in) p = (R)0;
+      if (ADJ && !in) { q = (R)0; a = (R)0; b = (R)0; }
+    }
     Vec3<R> ps = p;
     if constexpr (ADJ) ps = p * inv_kappa;
 #pragma unroll
@@ -1682,10 +1689,12 @@ __global__ __launch_bounds__(256) void k_stage_batch(const BatchJob* __restrict_
 // stage: 0 for an Euler step, else Runge-Kutta stage 1..4 of step t.  Record
 // r = spt t + stage - 1 (stage 0: r = t) is read, record r + 1 written (the
 // next stage's state, or after the last stage the state of step t + 1).
-template <typename R, int D>
+// (BW: waves per workgroup of the block kernels.)
+template <typename R, int D, int BW = 1>
 __device__ __forceinline__ FwdArgs batch_fwd_args(const BatchJob& b, int t, int stage) {
   FwdArgs A{};
   A.n = b.n; A.ig = b.row.ig; A.jg = b.row.jg;
+  A.nb = b.nb; A.S = 1; A.chunk = b.n; A.wchunk = (b.n + BW - 1) / BW;
   A.dim = D;
   A.rk = stage;
   A.rk_acc = b.rk_acc;
@@ -1703,10 +1712,11 @@ __device__ __forceinline__ FwdArgs batch_fwd_args(const BatchJob& b, int t, int 
 // Adjoint launches run t = T-1 .. 0 (and stages 4 .. 1 within a Runge-Kutta
 // step); the loss kernel fills adjoint record buffer 0 for the first of them,
 // and each launch reads buffer (launch index & 1) and writes the other.
-template <typename R, int D>
+template <typename R, int D, int BW = 1>
 __device__ __forceinline__ AdjArgs batch_adj_args(const BatchJob& b, int t, int stage, int T) {
   AdjArgs A{};
   A.n = b.n; A.ig = b.row.ig; A.jg = b.row.jg;
+  A.nb = b.nb; A.S = 1; A.chunk = b.n; A.wchunk = (b.n + BW - 1) / BW;
   A.dim = D;
   A.rk = stage;
   A.rk_lam = b.rk_lam;
@@ -1730,9 +1740,6 @@ __device__ __forceinline__ AdjArgs batch_adj_args(const BatchJob& b, int t, int 
 // left to balance at the end are short ones; the state is loaded after the sums
 // (other workgroups cover its latency, and the registers are worth more).  FP32's
 // occupancy is what its registers allow without spills.  What bounds it: issue.
-// Eight jobs of 500 to 8000 landmarks took 77 and 146 us per forward and adjoint
-// step with a workgroup per 64 landmarks, whose uneven lengths left half the chip
-// idle (41 and 81 us at the rate of the 65536-landmark kernels).
 template <typename R, int D, bool ADJ, bool RKS>
 __global__ __launch_bounds__(64 * kBatchWaves,
                              sizeof(R) == 8 ? 1 : ADJ ? 4 : 5) void k_batch(const BatchJob* __restrict__ J,
@@ -1752,12 +1759,29 @@ __global__ __launch_bounds__(64 * kBatchWaves,
   }
 }
 
+// The block kernels (batch_blocks): an item is one i-block of 64 landmarks, a
+// workgroup of BW waves that splits the j.  Their loops are the split kernels'.
+template <typename R, bool COMP, int D, bool ADJ, bool RKS>
+__global__ __launch_bounds__(64 * batch_waves(COMP, RKS)) void k_batch_blocks(
+    const BatchJob* __restrict__ J, const int2* __restrict__ items, const int* __restrict__ nitems,
+    int t, int stage, int T) {
+  constexpr int BW = batch_waves(COMP, RKS);
+  __shared__ typename AccOf<R, COMP>::type red[BW * (ADJ ? 9 : 6) * 64];
+  if ((int)blockIdx.x >= nitems[D == 2 ? 1 : 0]) return;
+  const int2 it = items[(D == 2 ? nitems[0] : 0) + (int)blockIdx.x];
+  const BatchJob& b = J[it.x];
+  if (!job_live(b)) return;
+  if constexpr (ADJ)
+    adj_block<R, COMP, RKS, BW, D>(batch_adj_args<R, D, BW>(b, t, stage, T), it.y, 0, red);
+  else fwd_block<R, COMP, RKS, BW, D>(batch_fwd_args<R, D, BW>(b, t, stage), it.y, 0, red);
+}
+
 template <typename R>
 __global__ __launch_bounds__(kLossThreads) void k_loss_batch(const BatchJob* __restrict__ J) {
   __shared__ double red[2 * kLossThreads];
   const BatchJob& b = J[blockIdx.x];
   if (!job_live(b)) return;
-  loss_body<R>(b.n, b.row.groups, b.lambda, b.st, b.xc, b.cen, b.h0p, b.ad, static_cast<Rec<R>*>(b.arec),
+  loss_body<R>(b.n, b.nh, b.lambda, b.st, b.xc, b.cen, b.h0p, b.ad, static_cast<Rec<R>*>(b.arec),
                b.out3, b.q1, nullptr, b.flag, nullptr, nullptr, nullptr, 0.0,
                b.spt == 4 ? b.sc.dt / 6.0 : 1.0, red);
 }
@@ -2032,37 +2056,45 @@ hipError_t launch_stage_batch(int mode, const BatchJob* jobs, int max_slots, int
   return hipGetLastError();
 }
 
-template <typename R, int D, bool ADJ>
-void batch_dispatch(const BatchJob* jobs, const int2* items, const int* nitems, int capacity,
-                    int t, int stage, int T, hipStream_t s) {
-  constexpr int kThreads = 64 * kBatchWaves;
-  const int grid = min(capacity, kBatchGrid);
-  if (stage > 0) k_batch<R, D, ADJ, true><<<grid, kThreads, 0, s>>>(jobs, items, nitems, t, stage, T);
-  else k_batch<R, D, ADJ, false><<<grid, kThreads, 0, s>>>(jobs, items, nitems, t, 0, T);
+template <typename R, bool COMP, int D, bool ADJ>
+void batch_dispatch(bool blocks, const BatchJob* jobs, const int2* items, const int* nitems,
+                    int capacity, int t, int stage, int T, hipStream_t s) {
+  const auto launch = [&](auto* k, int grid, int waves) {
+    k<<<grid, 64 * waves, 0, s>>>(jobs, items, nitems, t, stage, T);
+  };
+  const int rows = min(capacity, kBatchGrid);
+  if (blocks && stage > 0)
+    launch(k_batch_blocks<R, COMP, D, ADJ, true>, capacity, batch_waves(COMP, true));
+  else if (blocks) launch(k_batch_blocks<R, COMP, D, ADJ, false>, capacity, batch_waves(COMP, false));
+  else if (stage > 0) launch(k_batch<R, D, ADJ, true>, rows, kBatchWaves);
+  else launch(k_batch<R, D, ADJ, false>, rows, kBatchWaves);
 }
 
-template <bool ADJ>
-hipError_t launch_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
-                        const int* nitems, int capacity, int t, int stage, int T, hipStream_t s) {
-  if (dim != 2 && dim != 3) return hipErrorInvalidValue;
-  const bool f64 = mode == kFP64;
-  if (f64 && dim == 3)
-    batch_dispatch<double, 3, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
-  else if (f64) batch_dispatch<double, 2, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
-  else if (dim == 3) batch_dispatch<float, 3, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
-  else batch_dispatch<float, 2, ADJ>(jobs, items, nitems, capacity, t, stage, T, s);
+template <bool ADJ, int D>
+hipError_t batch_mode(int mode, bool blocks, const BatchJob* jobs, const int2* items,
+                      const int* nitems, int capacity, int t, int stage, int T, hipStream_t s) {
+  switch (mode) {
+    case kFP32: batch_dispatch<float, false, D, ADJ>(blocks, jobs, items, nitems, capacity, t, stage, T, s); break;
+    case kFP32Comp: batch_dispatch<float, true, D, ADJ>(blocks, jobs, items, nitems, capacity, t, stage, T, s); break;
+    case kFP64: batch_dispatch<double, false, D, ADJ>(blocks, jobs, items, nitems, capacity, t, stage, T, s); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_fwd_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
+hipError_t launch_fwd_batch(int mode, int dim, bool blocks, const BatchJob* jobs, const int2* items,
                             const int* nitems, int capacity, int t, int stage, hipStream_t s) {
-  return launch_batch<false>(mode, dim, jobs, items, nitems, capacity, t, stage, 0, s);
+  if (dim == 2) return batch_mode<false, 2>(mode, blocks, jobs, items, nitems, capacity, t, stage, 0, s);
+  if (dim == 3) return batch_mode<false, 3>(mode, blocks, jobs, items, nitems, capacity, t, stage, 0, s);
+  return hipErrorInvalidValue;
 }
 
-hipError_t launch_adj_batch(int mode, int dim, const BatchJob* jobs, const int2* items,
+hipError_t launch_adj_batch(int mode, int dim, bool blocks, const BatchJob* jobs, const int2* items,
                             const int* nitems, int capacity, int t, int stage, int T,
                             hipStream_t s) {
-  return launch_batch<true>(mode, dim, jobs, items, nitems, capacity, t, stage, T, s);
+  if (dim == 2) return batch_mode<true, 2>(mode, blocks, jobs, items, nitems, capacity, t, stage, T, s);
+  if (dim == 3) return batch_mode<true, 3>(mode, blocks, jobs, items, nitems, capacity, t, stage, T, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_loss_batch(int mode, const BatchJob* jobs, int max_slots, hipStream_t s) {

@@ -1,5 +1,5 @@
-"""The batched row kernels at the sizes where a job's plan changes, against the
-oracle's solver.
+"""The batched kernels at the sizes where a job's plan changes, against the oracle's
+solver: row items in a server of few slots, 64-landmark blocks in one of many.
 
 One optimiser iteration from p0 = 0 leaves a multiple of the first gradient in
 p0, so its direction is compared as a gradient is; tolerances are the library's
@@ -20,17 +20,19 @@ pytestmark = pytest.mark.gpu
 CASES = [("fp32c", n) for n in (1, 3, 64, 65, 257, 8191, 8192, 9300, 16383, 16385)]
 CASES += [("fp64", n) for n in (1, 5, 65, 8193, 16385)] + [("fp32", 65), ("fp32", 16385)]
 CASES += [("planar", 130), ("planar", 9300)]
+BLOCKS = [("fp32c", 1), ("fp32c", 65), ("fp32c", 9300), ("fp64", 65), ("fp64", 1000), ("fp32", 1000),
+          ("planar", 130)]
 
 
-@pytest.mark.parametrize("mode,n", CASES)
-def test_served_step_matches_oracle(orc_mt, mode, n):
+@pytest.mark.parametrize("slots,mode,n", [(2, *c) for c in CASES] + [(64, *c) for c in BLOCKS])
+def test_served_step_matches_oracle(orc_mt, slots, mode, n):
     from paper_1907_04839_amd import lddmm
     T = 1
     pb = synth.random_problem(7000 + n, n, T=T)
     dim = 3
     if mode == "planar":
         pb, dim, mode = synth.planar(pb), 2, "fp32c"
-    with lddmm.Server(T, mode, max_slots=2, max_n=20000, hbm_budget_bytes=128 << 20) as s:
+    with lddmm.Server(T, mode, max_slots=slots, max_n=20000, hbm_budget_bytes=128 << 20) as s:
         jid = s.submit(pb.q0, pb.target, pb.sigma, pb.lam, max_iter=1, dim=dim)
         r = s.result(jid, timeout=120)
     o = orc_mt.solve(pb.q0, pb.target, pb.sigma, pb.lam, T, orc_mt.SolveOpts(max_iter=1))
