@@ -215,6 +215,14 @@ inline int batch_groups(int max_n) {
   return g;
 }
 
+// Landmark (before the clamp to n - 1) whose state lane `lane` of the wave that ends a
+// row workgroup's step loads: its own row, or the workgroup's last one for the
+// lanes beyond the workgroup's `rows`.  Other workgroups store the other rows'
+// state in the same launch, so none of those may be read.
+constexpr int row_state(int row0, int rows, int lane) {
+  return row0 + (lane < rows ? lane : rows - 1);
+}
+
 inline Scales make_scales(double sigma, int T) {
   Scales s{};
   const double log2e = 1.4426950408889634;

@@ -305,7 +305,8 @@ __device__ __forceinline__ void block_combine_store(Acc* red, const Acc o[NC], i
 struct FwdState { double q[3], p[3], acc[6]; };
 struct AdjState { double a[3], b[3], hp0[3], hq0[3], lam[6]; };
 
-// (i is clamped: lanes without a landmark load the last one's state.)
+// (i is clamped: lanes without a landmark load the last one's state.  No lane may ask
+// for a landmark that another workgroup of the launch updates.)
 template <bool RKS>
 __device__ __forceinline__ FwdState load_fwd_state(const FwdArgs& A, int i) {
   FwdState v;
@@ -846,7 +847,8 @@ __device__ __forceinline__ void fwd_rows(const FwdArgs& A, int g, R* red, double
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row0 = g * A.ig * M, nt = (A.n + 63) >> 6;
   FwdState v{};
-  if (!BATCH && w == 0) v = load_fwd_state<RKS>(A, row0 + lane);   // its latency under the sums
+  if (!BATCH && w == 0)   // its latency under the sums
+    v = load_fwd_state<RKS>(A, row_state(row0, A.ig * M, lane));
   const int step = BATCH ? kTile * A.jg : nt;
   for (int t0 = 0; t0 < nt; t0 += step) {
     R h[row_pad<D, M>];
@@ -856,7 +858,7 @@ __device__ __forceinline__ void fwd_rows(const FwdArgs& A, int g, R* red, double
     if (!BATCH) break;
   }
   if (w == 0) {
-    if (BATCH) v = load_fwd_state<RKS>(A, row0 + lane);
+    if (BATCH) v = load_fwd_state<RKS>(A, row_state(row0, A.ig * M, lane));
     const bool own = lane < A.ig * M && row0 + lane < A.n;
     double hp[3] = {0.0, 0.0, 0.0}, hq[3] = {0.0, 0.0, 0.0};
     if (own)
@@ -874,7 +876,8 @@ __device__ __forceinline__ void adj_rows(const AdjArgs& A, int g, R* red, double
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int row0 = g * A.ig * M, nt = (A.n + 63) >> 6;
   AdjState v{};
-  if (!BATCH && w == 0) v = load_adj_state<RKS>(A, row0 + lane);   // its latency under the sums
+  if (!BATCH && w == 0)   // its latency under the sums
+    v = load_adj_state<RKS>(A, row_state(row0, A.ig * M, lane));
   const int step = BATCH ? kTile * A.jg : nt;
   for (int t0 = 0; t0 < nt; t0 += step) {
     R h[row_pad<D, M>];
@@ -884,7 +887,7 @@ __device__ __forceinline__ void adj_rows(const AdjArgs& A, int g, R* red, double
     if (!BATCH) break;
   }
   if (w == 0 && lane < A.ig * M && row0 + lane < A.n) {
-    if (BATCH) v = load_adj_state<RKS>(A, row0 + lane);
+    if (BATCH) v = load_adj_state<RKS>(A, row_state(row0, A.ig * M, lane));
     double sa[3] = {0.0, 0.0, 0.0}, sb[3] = {0.0, 0.0, 0.0};
     for (int c = 0; c < D; ++c) {
       sa[c] = fin[row_at<D, M>(lane) + c];
