@@ -16,6 +16,11 @@ namespace lddmm {
 // every mode).
 enum Mode : int { kFP32 = 0, kFP32Comp = 1, kFP64 = 2 };
 
+// Pairs in an FP32 sum, at most, before it is added in FP64 (compensated mode): a
+// multiple of the split loops' unroll depths (6 and 3), so that no tile of theirs
+// ends in a partial iteration.
+constexpr int kTile = 72;
+
 // Work decomposition of one N x N pair sum.  Landmark i is owned by lane
 // (i mod 64) of a wave of i-block ib = i / 64; the j range is split into S
 // chunks (one workgroup each) and, inside a workgroup, over W waves.
@@ -214,6 +219,14 @@ inline int batch_groups(int max_n) {
     if (last[k] < max_n && batch_plan(last[k]).groups > g) g = batch_plan(last[k]).groups;
   return g;
 }
+
+// Tiles that a wave of a batched row kernel sums before it adds them in FP64.  In FP32
+// the sums of four lanes are added first, so a lane takes a quarter of kTile.  The rms
+// error of A1 / kappa - A2 is 0.85 to 0.91 of the block kernels' (8000 to 32000
+// landmarks; 1.0 to 1.5 with kTile tiles, and both terms share a sum here).  It costs
+// nothing up to 4096 landmarks and 1 to 3 % above (ms, rounds of 72 | 18: eight jobs of
+// 500 to 8000 35.3 | 34.9, eight of 8000 at T = 20 68.2 | 70.2).
+constexpr int batch_round(bool f64) { return f64 ? kTile : kTile / 4; }
 
 // Landmark (before the clamp to n - 1) whose state lane `lane` of the wave that ends a
 // row workgroup's step loads: its own row, or the workgroup's last one for the

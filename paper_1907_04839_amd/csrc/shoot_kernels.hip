@@ -46,9 +46,6 @@ namespace lddmm {
 
 namespace {
 
-// pairs per FP32 tile in compensated mode: a multiple of both loops' unroll
-// depths (6 and 3), so that no tile ends in a partial iteration
-constexpr int kTile = 72;
 constexpr int kLossThreads = 1024;
 
 // Point record: (k q, 0, p, 0) for the trajectory, (a, 0, b_hat, 0) for the
@@ -730,16 +727,37 @@ __device__ __forceinline__ void adj_term(const R* x, const R* y, const R* pi, Ve
   for (int c = 0; c < D; ++c) h[D + c] = fma(g, w[c], h[D + c]);
 }
 
-// Sums of one wave: rows i0 .. i0 + M - 1 over the tiles t = t0, t0 + JG, ... < t1.
+// Adds the four quarters of a wave: lanes 16 g .. 16 g + 15 of h[k] then hold value
+// k + Q g (Q = row_pad / 4).  In FP32 an entry is the sum of four lanes' terms.
+template <typename R, int D, int M>
+__device__ __forceinline__ void row_exchange(R h[row_pad<D, M>]) {
+  constexpr int NV = row_pad<D, M>, Q = NV / 4;
+#pragma unroll
+  for (int k = 0; k < NV / 2; ++k) h[k] = swap32_add(h[k], h[k + NV / 2]);
+#pragma unroll
+  for (int k = 0; k < Q; ++k) h[k] = swap16_add(h[k], h[k + Q]);
+}
+
+// What a row workgroup keeps of its waves' sums: the values themselves, or, in the
+// batched kernels, their FP64 sums over the rounds.
+template <typename R, bool BATCH>
+using RowRed = typename std::conditional<BATCH, double, R>::type;
+
+// Sums of one wave: rows i0 .. i0 + M - 1 over the tiles t = t0, t0 + JG, ... < t1,
+// exchanged and stored to the lane's slots own[64 k].
 // ADJ: h[m] = {A1 / kappa - A2 (D components), B (D)}, else {Hp (D), Hq's sums (D)}.
-// BATCH: the pointers come from a descriptor in memory, and the compiler would hold
+// BATCH: n may be large, so the tiles are taken batch_round at a time and each round's
+// sums are added to the slots in FP64 (no barrier: a lane reads back what it wrote),
+// which keeps an FP32 sum to kTile pairs.  The row plans end before that, and with
+// the loop around them their adjoint took 10 % longer (n = 1847).
+// The batched pointers come from a descriptor in memory, and the compiler would hold
 // the rows in vector registers for fear of the stores; through the constant address
 // space (records of the step are not written by its launch) they become scalar
 // loads (eight jobs of 500 to 8000: 38.9 -> 37.1 ms, FP64 24.2 -> 22.2).
 template <typename R, bool ADJ, int D, int M, bool BATCH>
 __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, int i0, int t0,
                                          int t1, int JG, int lane, R inv_kappa,
-                                         R h[row_pad<D, M>]) {
+                                         RowRed<R, BATCH>* own) {
   const GlobalPtr<Rec<R>> X = global_ptr(static_cast<const Rec<R>*>(Xv));
   const GlobalPtr<Rec<R>> Y = global_ptr(static_cast<const Rec<R>*>(Yv));
   R xi[M][6], yi[M][6];
@@ -755,8 +773,6 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
       yi[m][3] = in_vgpr(b.px); yi[m][4] = in_vgpr(b.py); yi[m][5] = in_vgpr(b.pz);
     }
   }
-#pragma unroll
-  for (int k = 0; k < row_pad<D, M>; ++k) h[k] = (R)0;
   struct Tile { Vec3<R> q, p, a, b; };
   // 32-bit byte offsets from a scalar base: an address is one instruction (with the
   // narrower mask below 2-4 % of a step, FP64 n = 2500 forward 14.1 -> 12.8 us)
@@ -778,48 +794,55 @@ __device__ __forceinline__ void row_sums(const void* Xv, const void* Yv, int n, 
   const unsigned end = (unsigned)(n - 1) * kRec;
   unsigned o = (unsigned)(t0 * 64 + lane) * kRec;
   Tile next = load(min(o, end));
-  for (int t = t0; t < t1; t += JG) {
-    const bool in = o <= end;
-    const Tile cur = next;
-    o += 64 * kRec * (unsigned)JG;
-    next = load(min(o, end));
-    Vec3<R> q = cur.q, p = cur.p, a = (R)0, b = (R)0;
-    if constexpr (ADJ) { a = cur.a; b = cur.b; }
-    // Lanes beyond n add an exact 0 to every sum with p_j = a_j = 0.  In the batched
-    // kernels a branch keeps that to the ragged tile (eight jobs of 500 to 8000: 36.0
-    // -> 34.4 ms); in the others the adjoint's loop comes out slower then (n = 2500
-    // 9.7 -> 11.7 us per step), and slower too when it does not zero q and b (2D n = 3000
-    // 9.8 -> 10.8).
-    if constexpr (BATCH) {
-      if (t * 64 + 64 > n && !in) { p = (R)0; a = (R)0; }
-    } else {
-      if (!in) p = (R)0;
-      if (ADJ && !in) { q = (R)0; a = (R)0; b = (R)0; }
-    }
-    Vec3<R> ps = p;
-    if constexpr (ADJ) ps = p * inv_kappa;
+  int t = t0;
+  bool first = true;
+  do {
+    const int te = BATCH ? min(t1, t + batch_round(std::is_same<R, double>::value) * JG) : t1;
+    R h[row_pad<D, M>];
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-      if constexpr (ADJ) adj_term<R, D>(xi[m], yi[m], &xi[m][3], q, p, ps, a, b, h + 2 * D * m);
-      else fwd_term<R, D>(xi[m], q, p, h + 2 * D * m);
+    for (int k = 0; k < row_pad<D, M>; ++k) h[k] = (R)0;
+    for (; t < te; t += JG) {
+      const bool in = o <= end;
+      const Tile cur = next;
+      o += 64 * kRec * (unsigned)JG;
+      next = load(min(o, end));
+      Vec3<R> q = cur.q, p = cur.p, a = (R)0, b = (R)0;
+      if constexpr (ADJ) { a = cur.a; b = cur.b; }
+      // Lanes beyond n add an exact 0 to every sum with p_j = a_j = 0.  In the batched
+      // kernels a branch keeps that to the ragged tile (eight jobs of 500 to 8000: 36.0
+      // -> 34.4 ms); in the others the adjoint's loop comes out slower then (n = 2500
+      // 9.7 -> 11.7 us per step), and slower too when it does not zero q and b (2D n = 3000
+      // 9.8 -> 10.8).
+      if constexpr (BATCH) {
+        if (t * 64 + 64 > n && !in) { p = (R)0; a = (R)0; }
+      } else {
+        if (!in) p = (R)0;
+        if (ADJ && !in) { q = (R)0; a = (R)0; b = (R)0; }
+      }
+      Vec3<R> ps = p;
+      if constexpr (ADJ) ps = p * inv_kappa;
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        if constexpr (ADJ) adj_term<R, D>(xi[m], yi[m], &xi[m][3], q, p, ps, a, b, h + 2 * D * m);
+        else fwd_term<R, D>(xi[m], q, p, h + 2 * D * m);
+      }
     }
-  }
+    row_exchange<R, D, M>(h);
+#pragma unroll
+    for (int k = 0; k < row_pad<D, M> / 4; ++k) {
+      if (BATCH && !first) own[k * 64] += (RowRed<R, BATCH>)h[k];
+      else own[k * 64] = (RowRed<R, BATCH>)h[k];
+    }
+    first = false;
+  } while (BATCH && t < t1);
 }
 
-// The workgroup's sums of rows [0, M ig) in fin (row_at), from every wave's h;
-// added to what fin holds with `add`.
-template <typename R, int D, int M>
-__device__ __forceinline__ void row_combine(R h[row_pad<D, M>], R* red, double* fin, int ig, int jg,
-                                            int w, int lane, bool add) {
+// The workgroup's sums of rows [0, M ig) in fin (row_at), from every wave's
+// exchanged values in red.
+template <typename T, int D, int M>
+__device__ __forceinline__ void row_combine(const T* red, double* fin, int ig, int jg, int w,
+                                            int lane) {
   constexpr int NV = row_pad<D, M>, Q = NV / 4;
-  R* f = h;
-#pragma unroll
-  for (int k = 0; k < NV / 2; ++k) f[k] = swap32_add(f[k], f[k + NV / 2]);
-#pragma unroll
-  for (int k = 0; k < Q; ++k) f[k] = swap16_add(f[k], f[k + Q]);
-  // lanes 16 g .. 16 g + 15 now hold value k + Q g of the wave in f[k]
-#pragma unroll
-  for (int k = 0; k < Q; ++k) red[(w * Q + k) * 64 + lane] = f[k];
   __syncthreads();
   for (int kk = w; kk < Q * ig; kk += ig * jg) {
     const int k = kk % Q, g = kk / Q;
@@ -829,34 +852,31 @@ __device__ __forceinline__ void row_combine(R h[row_pad<D, M>], R* red, double* 
     s = row_add<0x122>(s);
     s = row_add<0x124>(s);
     s = row_add<0x128>(s);
-    if ((lane & 15) == 0) {
-      double* f = fin + g * NV + k + Q * (lane >> 4);
-      *f = add ? *f + s : s;
-    }
+    if ((lane & 15) == 0) fin[g * NV + k + Q * (lane >> 4)] = s;
   }
   __syncthreads();
 }
 
-// A step of the rows of workgroup item g, in ig x jg waves.  BATCH: n may be
-// large, so a wave's tiles are taken kTile at a time and no FP32 sum is longer
-// than kTile terms; the row plans end before that, and with the loop around them
-// their adjoint took 10 % longer (n = 1847).
+// Combined sums (fin) of the rows of a workgroup item, in ig x jg waves.
+template <typename R, bool ADJ, int D, int M, bool BATCH>
+__device__ __forceinline__ void row_step(const void* X, const void* Y, int n, int ig, int jg,
+                                         int row0, R inv_kappa, RowRed<R, BATCH>* red, double* fin,
+                                         int w, int lane) {
+  row_sums<R, ADJ, D, M, BATCH>(X, Y, n, row0 + (w % ig) * M, w / ig, (n + 63) >> 6, jg, lane,
+                                inv_kappa, red + w * (row_pad<D, M> / 4) * 64 + lane);
+  row_combine<RowRed<R, BATCH>, D, M>(red, fin, ig, jg, w, lane);
+}
+
 template <typename R, bool RKS, int D, int M, bool BATCH = false>
-__device__ __forceinline__ void fwd_rows(const FwdArgs& A, int g, R* red, double* fin) {
+__device__ __forceinline__ void fwd_rows(const FwdArgs& A, int g, RowRed<R, BATCH>* red,
+                                         double* fin) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int row0 = g * A.ig * M, nt = (A.n + 63) >> 6;
+  const int row0 = g * A.ig * M;
   FwdState v{};
   if (!BATCH && w == 0)   // its latency under the sums
     v = load_fwd_state<RKS>(A, row_state(row0, A.ig * M, lane));
-  const int step = BATCH ? kTile * A.jg : nt;
-  for (int t0 = 0; t0 < nt; t0 += step) {
-    R h[row_pad<D, M>];
-    row_sums<R, false, D, M, BATCH>(A.rec_t, nullptr, A.n, row0 + (w % A.ig) * M, t0 + w / A.ig,
-                             BATCH ? min(nt, t0 + step) : nt, A.jg, lane, (R)0, h);
-    row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane, BATCH && t0 > 0);
-    if (!BATCH) break;
-  }
+  row_step<R, false, D, M, BATCH>(A.rec_t, nullptr, A.n, A.ig, A.jg, row0, (R)0, red, fin, w, lane);
   if (w == 0) {
     if (BATCH) v = load_fwd_state<RKS>(A, row_state(row0, A.ig * M, lane));
     const bool own = lane < A.ig * M && row0 + lane < A.n;
@@ -871,21 +891,16 @@ __device__ __forceinline__ void fwd_rows(const FwdArgs& A, int g, R* red, double
 }
 
 template <typename R, bool RKS, int D, int M, bool BATCH = false>
-__device__ __forceinline__ void adj_rows(const AdjArgs& A, int g, R* red, double* fin) {
+__device__ __forceinline__ void adj_rows(const AdjArgs& A, int g, RowRed<R, BATCH>* red,
+                                         double* fin) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int row0 = g * A.ig * M, nt = (A.n + 63) >> 6;
+  const int row0 = g * A.ig * M;
   AdjState v{};
   if (!BATCH && w == 0)   // its latency under the sums
     v = load_adj_state<RKS>(A, row_state(row0, A.ig * M, lane));
-  const int step = BATCH ? kTile * A.jg : nt;
-  for (int t0 = 0; t0 < nt; t0 += step) {
-    R h[row_pad<D, M>];
-    row_sums<R, true, D, M, BATCH>(A.rec_t, A.arec, A.n, row0 + (w % A.ig) * M, t0 + w / A.ig,
-                            BATCH ? min(nt, t0 + step) : nt, A.jg, lane, (R)(1.0 / A.sc.kappa), h);
-    row_combine<R, D, M>(h, red, fin, A.ig, A.jg, w, lane, BATCH && t0 > 0);
-    if (!BATCH) break;
-  }
+  row_step<R, true, D, M, BATCH>(A.rec_t, A.arec, A.n, A.ig, A.jg, row0, (R)(1.0 / A.sc.kappa), red,
+                                 fin, w, lane);
   if (w == 0 && lane < A.ig * M && row0 + lane < A.n) {
     if (BATCH) v = load_adj_state<RKS>(A, row_state(row0, A.ig * M, lane));
     double sa[3] = {0.0, 0.0, 0.0}, sb[3] = {0.0, 0.0, 0.0};
@@ -1750,7 +1765,7 @@ __global__ __launch_bounds__(64 * kBatchWaves,
                                                             const int* __restrict__ nitems, int t,
                                                             int stage, int T) {
   constexpr int M = kBatchRows;
-  __shared__ R red[kBatchWaves * (row_pad<D, M> / 4) * 64];
+  __shared__ double red[kBatchWaves * (row_pad<D, M> / 4) * 64];
   __shared__ double fin[kBatchWaves * row_pad<D, M>];
   const int2* it = items + (D == 2 ? nitems[0] : 0);
   const int count = nitems[D == 2 ? 1 : 0];
