@@ -144,8 +144,10 @@ inline void widen_plan(Plan& p, int mode, bool rk) {
 // records in the CU's cache (n = 1847: 266 -> 256 us; FP64 475 -> 418).  FP64 waves
 // hold twice the registers: 8 per workgroup at most.  In FP32 workgroups of four
 // waves are the better ones from n = 3073 on, where several share a CU and a wave
-// still has 12 tiles or more (n = 4096 624 -> 605, 5000 855 -> 833; but 3001 410 ->
-// 442, 2500 341 -> 387).
+// still has 12 tiles or more (n = 4096 624 -> 605; but 3001 410 -> 442, 2500 341 ->
+// 387).  They end at 72 tiles: the FP32 sums are those of four lanes, of a quarter
+// of the tiles each, and cover kTile pairs at most (T = 12, four | eight waves: n =
+// 4608 469 | 496, 5000 517 | 532).
 inline RowPlan row_plan(int n, int mode) {
   constexpr int kCUs = 256;   // MI355X
   const bool f64 = mode == kFP64;
@@ -163,7 +165,7 @@ inline RowPlan row_plan(int n, int mode) {
   }
   const int g = groups(r.m), tiles = (n + 63) / 64;
   r.ig = g > kCUs && g <= 2 * kCUs ? 2 : 1;
-  r.jg = (f64 ? g > kCUs : n > 3072) ? 4 : 8;
+  r.jg = (f64 ? g > kCUs : n > 3072 && tiles <= kTile) ? 4 : 8;
   if (r.jg > tiles) r.jg = tiles;
   r.groups = groups(r.m * r.ig);
   return r;

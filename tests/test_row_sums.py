@@ -37,6 +37,16 @@ def test_a_served_fp32_sum_covers_72_pairs_at_most(plan):
         assert tile == 72 and pairs <= tile, (n, pairs)
 
 
+def test_a_row_plans_fp32_sum_covers_72_pairs_at_most(tmp_path):
+    exe = tmp_path / "row_pairs_test"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_1907_04839_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "cpp", "row_pairs_test.cpp"), "-o", str(exe)],
+                   check=True)
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and "row pairs ok" in out.stdout, out.stdout
+
+
 def row_sums(terms, jg, round_):
     """Sums over axis 1 of the terms ([rows, n] each, added one after the other)."""
     rows, n = terms[0].shape
