@@ -174,10 +174,11 @@ struct BatchJob {
 // Waves per workgroup of the block kernels of a batch.  On the 48-job serving
 // stream (FP32-compensated, Euler steps) 12-wave workgroups gave 15.7 solves/s
 // against 14.9 for 8-wave and 13.8 for 16-wave ones: two 12-wave workgroups
-// fill the 24 wave slots per CU that the adjoint's registers leave.  FP32,
-// FP64 and Runge-Kutta stage instances keep 8 (their registers differ; 12 was
-// measured only in the FP32-compensated Euler case).
-constexpr int batch_waves(bool compensated, bool rk) { return compensated && !rk ? 12 : 8; }
+// fill the 24 wave slots per CU that the adjoint's registers leave.  With
+// Runge-Kutta stages 12 waves took 0.77 to 0.99 of the time of 8 (2 to 64 jobs of
+// 500 to 16384 landmarks, 3D and planar).  FP64 instances keep 8 (their registers
+// allow no more per CU).
+constexpr int batch_waves(bool compensated) { return compensated ? 12 : 8; }
 
 // Launch shapes of a batch of at most max_slots jobs with n <= max_n:
 // stage (max_n/256, max_slots), loss max_slots.  Pair kernels: `blocks`, capacity

@@ -1778,12 +1778,15 @@ __global__ __launch_bounds__(64 * kBatchWaves,
 }
 
 // The block kernels (batch_blocks): an item is one i-block of 64 landmarks, a
-// workgroup of BW waves that splits the j.  Their loops are the split kernels'.
+// workgroup of BW waves that splits the j.  Their loops are the split kernels', in
+// FP32 the compensated ones for both modes: a job's accuracy must not follow from the
+// server's size, and 12 waves of them are the faster ones too (solves of 2 to 64 jobs
+// in 0.53 to 1.03 of the time of the 8-wave running sums, most below 0.95).
 template <typename R, bool COMP, int D, bool ADJ, bool RKS>
-__global__ __launch_bounds__(64 * batch_waves(COMP, RKS)) void k_batch_blocks(
+__global__ __launch_bounds__(64 * batch_waves(COMP)) void k_batch_blocks(
     const BatchJob* __restrict__ J, const int2* __restrict__ items, const int* __restrict__ nitems,
     int t, int stage, int T) {
-  constexpr int BW = batch_waves(COMP, RKS);
+  constexpr int BW = batch_waves(COMP);
   __shared__ typename AccOf<R, COMP>::type red[BW * (ADJ ? 9 : 6) * 64];
   if ((int)blockIdx.x >= nitems[D == 2 ? 1 : 0]) return;
   const int2 it = items[(D == 2 ? nitems[0] : 0) + (int)blockIdx.x];
@@ -2082,8 +2085,8 @@ void batch_dispatch(bool blocks, const BatchJob* jobs, const int2* items, const 
   };
   const int rows = min(capacity, kBatchGrid);
   if (blocks && stage > 0)
-    launch(k_batch_blocks<R, COMP, D, ADJ, true>, capacity, batch_waves(COMP, true));
-  else if (blocks) launch(k_batch_blocks<R, COMP, D, ADJ, false>, capacity, batch_waves(COMP, false));
+    launch(k_batch_blocks<R, COMP, D, ADJ, true>, capacity, batch_waves(COMP));
+  else if (blocks) launch(k_batch_blocks<R, COMP, D, ADJ, false>, capacity, batch_waves(COMP));
   else if (stage > 0) launch(k_batch<R, D, ADJ, true>, rows, kBatchWaves);
   else launch(k_batch<R, D, ADJ, false>, rows, kBatchWaves);
 }
@@ -2092,7 +2095,7 @@ template <bool ADJ, int D>
 hipError_t batch_mode(int mode, bool blocks, const BatchJob* jobs, const int2* items,
                       const int* nitems, int capacity, int t, int stage, int T, hipStream_t s) {
   switch (mode) {
-    case kFP32: batch_dispatch<float, false, D, ADJ>(blocks, jobs, items, nitems, capacity, t, stage, T, s); break;
+    case kFP32:   // the same sums as kFP32Comp
     case kFP32Comp: batch_dispatch<float, true, D, ADJ>(blocks, jobs, items, nitems, capacity, t, stage, T, s); break;
     case kFP64: batch_dispatch<double, false, D, ADJ>(blocks, jobs, items, nitems, capacity, t, stage, T, s); break;
     default: return hipErrorInvalidValue;
