@@ -180,34 +180,50 @@ constexpr int kChainMax = 64;
 // kernels' faster loops (165 cycles per forward + adjoint pair against about 200)
 // but need many workgroups of them: one of n = 8000 keeps a CU for 46 us (forward),
 // more than the CU's share of such a batch.  How many jobs share the chip is what a
-// server's configuration says: rows up to max_slots ceil(max_n / 64) = 1024.  Solves, ms
-// (FP32-compensated, T = 40, 4 iterations; blocks | rows):
-//   8 slots: 500 to 8000 46.9 | 35.1, eight of 8000 133 | 138; 4 of 1500 11.7 | 6.4;
-//   1 of 2000 11.5 | 4.1; 32 slots: 500 to 8000 96 | 111; FP64 (T = 10) 500 to 8000
-//   38.1 | 21.3, eight of 8000 92 | 87.
-inline bool batch_blocks(int max_slots, int max_n) {
-  return (long long)max_slots * ((max_n + 63) / 64) > 1024;
+// server's configuration says, and a job's result must not follow from what else
+// runs, so the configuration alone decides.  Time of a solve with rows over blocks,
+// all slots full, of jobs of max_n | of max_n / 16 to max_n (Euler, 3D):
+//   FP32-compensated  500: 8 slots 0.76 | 0.70, 16 0.95 | 0.75, 32 1.31 | 0.87
+//     1000: 8 0.78 | 0.54, 12 0.99 | 0.60, 16 1.13 | 0.67, 32 1.31 | 0.86
+//     2000: 1 0.37, 8 0.94 | 0.50, 12 0.91 | 0.60, 16 1.07 | 0.68, 32 1.2 | 0.95
+//     4096: 1 0.46, 8 0.95 | 0.60, 12 1.02 | 0.74, 16 1.05 | 0.84
+//     8000: 1 0.67, 4 1.01 | 0.70, 8 1.04 to 1.08 | 0.78 (0.74 of 500 to 8000), 12
+//       1.08 | 0.88;  12000: 1 0.78, 5 1.02 | 0.78;  16000: 1 1.01, 4 1.07 | 0.93
+//     16384 (its blocks alone fill the 256 CUs): 1 1.15, 2 1.10;  65536: 1 1.11
+//   Runge-Kutta stages the same within 0.04; planar never above 0.96 up to 16000.
+//   FP64  1000: 16 slots 0.85 | 0.51, 24 0.95 | 0.57, 32 1.29 | 0.64;  4096: 16 0.95 |
+//     0.66;  8000: 8 0.92 | 0.64, 12 1.02 | 0.75, 16 1.06;  16384: 4 0.93;  65536: 0.97
+// Both sides of the lines lose something: eight equal jobs of 8000, whose blocks
+// happen to fill two rounds, against uneven ones there.
+inline bool batch_blocks(int max_slots, int max_n, int mode) {
+  const bool f64 = mode == kFP64;
+  return max_slots > (f64 ? 24 : 12) || (!f64 && max_n >= 16384) ||
+         (long long)max_slots * ((max_n + 63) / 64) > 1024;
 }
 
 // Row plans of the batched kernels: four waves of five rows per workgroup.
-// Measured as above (ms; eight jobs of 500 to 8000 landmarks, one of 2000, four of
-// 1500; 8-wave items before the loops' later steps):
+// Measured (ms; eight jobs of 500 to 8000 landmarks, one of 2000, four of 1500; T = 40,
+// 4 iterations; 8-wave items before the loops' later steps):
 //   8 waves, m = 5                         43.6   4.22  8.36
 //   2 waves, m = 5                         41.6   5.84  7.18
 //   4 waves, m = 4, 5, 6, 8                36.6, 34.4, 39.7, 41.2;  3.82, 4.12, 4.76,
 //                                          4.82;  6.12, 6.38, 6.80, 7.27
 // and FP64 (T = 10) blocks 38.1, 8.90, 9.05, rows 22.2, 1.77, 3.41 (m = 4).
 // The waves share the j tiles (jg = 4), which a job alone on the chip needs (one of
-// 2000 with jg = 1: 9.5 ms); from n = 8192 on there are rows enough to fill it
-// with two and then four i-groups, whose waves share their j records.
+// 2000 with jg = 1: 9.5 ms); more i-groups, whose waves share their j records and
+// whose workgroups end less often, are the better ones where there are rows enough
+// for them (jg = 4 | 2, T = 16: 12 of 4096 29.9 | 28.9, eight of 8000 56.1 | 53.9, one
+// of 8000 10.0 | 10.2, one of 4096 (T = 20) 4.65 | 4.63).
+// Workgroups of a launch: up to 4096 an item each, so that the hardware balances them
+// (2048, 4096, 65536: 12 of 2000 15.2, 14.0, 14.1; eight of 8000 56.1, 53.9, 53.9).
 constexpr int kBatchWaves = 4;
 constexpr int kBatchRows = 5;
-constexpr int kBatchGrid = 2048;   // workgroups of a launch, at most
+constexpr int kBatchGrid = 4096;
 
 inline RowPlan batch_plan(int n) {
   RowPlan r{};
   r.m = kBatchRows;
-  r.jg = n < 8192 ? 4 : n < 16384 ? 2 : 1;
+  r.jg = n < 3072 ? 4 : n < 16384 ? 2 : 1;
   r.ig = kBatchWaves / r.jg;
   r.groups = (n + r.m * r.ig - 1) / (r.m * r.ig);
   return r;
@@ -216,7 +232,7 @@ inline RowPlan batch_plan(int n) {
 // The most workgroups that a job of at most max_n landmarks has.
 inline int batch_groups(int max_n) {
   int g = batch_plan(max_n).groups;
-  const int last[2] = {8191, 16383};   // of the plans with more i-groups after them
+  const int last[2] = {3071, 16383};   // of the plans with more i-groups after them
   for (int k = 0; k < 2; ++k)
     if (last[k] < max_n && batch_plan(last[k]).groups > g) g = batch_plan(last[k]).groups;
   return g;

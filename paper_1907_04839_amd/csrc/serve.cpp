@@ -527,7 +527,7 @@ lddmm_status lddmm_server_create(const lddmm_server_config* cfg, lddmm_server** 
   s->t0 = Clock::now();
   const int M = cfg->max_slots;
   // items of the most that can run at once: M jobs of max_n landmarks
-  s->blocks = batch_blocks(M, cfg->max_n);
+  s->blocks = batch_blocks(M, cfg->max_n, cfg->precision);
   s->capacity = M * (s->blocks ? (cfg->max_n + 63) / 64 : batch_groups(cfg->max_n));
   s->tab.assign(M, BatchJob{});
   s->ltab.assign(M, LbfgsJob{});
