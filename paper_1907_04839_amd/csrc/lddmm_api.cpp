@@ -593,7 +593,9 @@ FlowArgs flow_args(const Job& j, int m) {
   a.m = m;
   a.slots = j.L.slots;
   a.spt = j.spt;
-  flow_chunks(a);
+  const FlowPlan f = flow_plan(j.p.n);
+  a.pairs = f.pairs;
+  a.clen = f.clen;
   a.dim = j.dim;
   a.k = j.sc.k;
   a.dt = j.sc.dt;

@@ -254,6 +254,21 @@ constexpr int row_state(int row0, int rows, int lane) {
   return row0 + (lane < rows ? lane : rows - 1);
 }
 
+// The point flow's cut of the landmarks, by their number alone: eight pairs of equal
+// chunks from 1024 landmarks on, before that chunks of 64 landmarks or more.
+// Chunks of whole 64-landmark tiles left waves idle just above multiples of 1024 and
+// made small sets run mostly padding (us, eight steps of 262144 points, FP32-compensated
+// n = 10 64 -> 33, 129 154 -> 114, 1025 625 -> 553; FP64 n = 300 642 -> 522, 4097 6975 ->
+// 6410).
+struct FlowPlan { int pairs, clen; };
+
+inline FlowPlan flow_plan(int n) {
+  FlowPlan f{1, 0};
+  while (f.pairs < 8 && f.pairs * 2 * 128 <= n) f.pairs *= 2;
+  f.clen = (n + 2 * f.pairs - 1) / (2 * f.pairs);
+  return f;
+}
+
 inline Scales make_scales(double sigma, int T) {
   Scales s{};
   const double log2e = 1.4426950408889634;

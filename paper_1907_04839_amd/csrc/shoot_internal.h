@@ -111,7 +111,7 @@ struct FlowArgs {
   int slots;            // trajectory slots: record r is slot r % slots
   int spt;              // records per step: 1 (Euler), 4 (Runge-Kutta stage states;
                         // record spt t + s is stage s + 1 of step t)
-  int pairs, clen;      // chunk pairs, landmarks per chunk (a multiple of 64)
+  int pairs, clen;      // chunk pairs, landmarks per chunk (flow_plan)
   int half;             // a wave sums one chunk (else a pair of them)
   int dim;              // 3, or 2 for planar problems
   double k, dt;
@@ -124,8 +124,6 @@ struct FlowArgs {
   double* v_part;       // [pairs][3][m], with v_out and split: the pairs' velocities
 };
 
-// Fills a's chunks for its n.
-void flow_chunks(FlowArgs& a);
 // With a.v_out and v_part room for [pairs][3][m] doubles, the pairs of a launch
 // too small for the chip are spread over workgroups and summed by a second one.
 hipError_t launch_flow(int mode, const FlowArgs& a, hipStream_t s, hipEvent_t* ev = nullptr);

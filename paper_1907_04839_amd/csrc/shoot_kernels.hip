@@ -1135,6 +1135,30 @@ template <int RP>
 constexpr int kFlowWaveLds = RP * 3 * 64 * 8;
 static_assert(sizeof(FlowTile<3>) <= kFlowWaveLds<1>, "a tile fits its wave's sums");
 
+// v += the first cnt landmarks of the tile for the lane's pre-scaled points xs.  FULL:
+// cnt is kFlowTile (a constant count takes 3 to 10 % less, n = 10007, m = 100000).
+template <int D, int RP, bool FULL>
+__device__ __forceinline__ void flow_tile(const FlowTile<D>& tile, const float xs[RP][3], int cnt,
+                                          float v[RP][3]) {
+#pragma unroll 2
+  for (int j = 0; j < (FULL ? kFlowTile : cnt); ++j) {
+    float q[3], p[3];
+    tile.get(j, q, p);
+#pragma unroll
+    for (int r = 0; r < RP; ++r) {
+      float r2 = 0.0f;
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        const float d = xs[r][c] - q[c];
+        r2 = c == 0 ? d * d : fma(d, d, r2);
+      }
+      const float g = ex2n(r2);
+#pragma unroll
+      for (int c = 0; c < D; ++c) v[r][c] = fma(g, p[c], v[r][c]);
+    }
+  }
+}
+
 // o += sum over landmarks [c0, c1) of g(x, q_j) p_j for the lane's pre-scaled
 // points xs.  FP32: tiles of 64 terms through the wave's LDS, each folded into FP64.
 template <int D, int RP>
@@ -1143,32 +1167,16 @@ __device__ __forceinline__ void flow_chunk(const Rec<float>* __restrict__ X, voi
                                            double o[RP][3]) {
   FlowTile<D>& tile = *static_cast<FlowTile<D>*>(lds);
   for (int s = c0; s < c1; s += kFlowTile) {
-    Rec<float> rec = X[min(s + lane, c1 - 1)];
-    if (s + lane >= c1) { rec.px = 0.0f; rec.py = 0.0f; rec.pz = 0.0f; }
-    tile.put(lane, rec);
+    const int cnt = min(kFlowTile, c1 - s);
+    tile.put(lane, X[min(s + lane, c1 - 1)]);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     float v[RP][3];
 #pragma unroll
     for (int r = 0; r < RP; ++r)
 #pragma unroll
       for (int c = 0; c < 3; ++c) v[r][c] = 0.0f;
-#pragma unroll 2
-    for (int j = 0; j < kFlowTile; ++j) {
-      float q[3], p[3];
-      tile.get(j, q, p);
-#pragma unroll
-      for (int r = 0; r < RP; ++r) {
-        float r2 = 0.0f;
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          const float d = xs[r][c] - q[c];
-          r2 = c == 0 ? d * d : fma(d, d, r2);
-        }
-        const float g = ex2n(r2);
-#pragma unroll
-        for (int c = 0; c < D; ++c) v[r][c] = fma(g, p[c], v[r][c]);
-      }
-    }
+    if (cnt == kFlowTile) flow_tile<D, RP, true>(tile, xs, cnt, v);
+    else flow_tile<D, RP, false>(tile, xs, cnt, v);
 #pragma unroll
     for (int r = 0; r < RP; ++r)
 #pragma unroll
@@ -2005,20 +2013,14 @@ hipError_t launch_adj_step(int mode, const Plan& p, const AdjArgs& a, hipStream_
   return hipErrorInvalidValue;
 }
 
-// Eight pairs of chunks from 1024 landmarks on; at least 64 landmarks per chunk.
-void flow_chunks(FlowArgs& a) {
-  int pairs = 1;
-  while (pairs < 8 && pairs * 2 * 128 <= a.n) pairs *= 2;
-  a.pairs = pairs;
-  a.clen = ((a.n + 2 * pairs - 1) / (2 * pairs) + kFlowTile - 1) / kFlowTile * kFlowTile;
-}
-
 // A wave per chunk while the points leave room for it (us per step at n = 4096:
 // m = 5003 47 -> 18, 20000 48 -> 32, 100000 129 -> 112; with a wave per pair of
 // chunks and two points per lane 41, 42, 124); two points per lane where that
 // fills its rounds of 1024 workgroups at least 0.94 as well as one per lane fills
-// its rounds of 512 (m = 262144: 275 -> 242, one per lane 258).  FP64 from 768
-// workgroups on: a wave per pair (velocity at m = 262144 779 us, per chunk 842).
+// its rounds of 512 (m = 262144: 275 -> 242, one per lane 258).  FP64: a wave
+// per pair from 2048 such waves on (velocity at n = 4096, m = 262144 779 us, per chunk
+// 842; Runge-Kutta flow at n = 10007, m = 20000, two steps, 2950 and 3120, where 16
+// waves leave a CU one workgroup).
 // A velocity of fewer than 512 workgroups is also spread by the pairs (n =
 // 4096, m = 5003 86 -> 29 us; n = 20000, m = 1000 136 -> 81, 105 without).
 hipError_t launch_flow(int mode, const FlowArgs& args, hipStream_t s, hipEvent_t* ev) {
@@ -2030,7 +2032,7 @@ hipError_t launch_flow(int mode, const FlowArgs& args, hipStream_t s, hipEvent_t
   const int b1 = (a.m + 63) / 64, b2 = (a.m + 127) / 128;
   const bool two = mode != kFP64 && a.pairs == 8 && b2 >= 1024 &&
                    filled(b2, 1024) >= 0.94 * filled(b1, 512);
-  a.half = two || (mode == kFP64 && b1 >= 768) ? 0 : 1;
+  a.half = two || (mode == kFP64 && b1 * a.pairs >= 2048) ? 0 : 1;
   int W = a.half ? 2 * a.pairs : a.pairs;
   dim3 grid((unsigned)(two ? b2 : b1));
   const bool split = a.v_part && a.v_out && a.half && W > 4 && b1 < 512;
