@@ -21,10 +21,6 @@ enum Mode : int { kFP32 = 0, kFP32Comp = 1, kFP64 = 2 };
 // ends in a partial iteration.
 constexpr int kTile = 72;
 
-// Work decomposition of one N x N pair sum.  Landmark i is owned by lane
-// (i mod 64) of a wave of i-block ib = i / 64; the j range is split into S
-// chunks (one workgroup each) and, inside a workgroup, over W waves.
-// Partial sums of different chunks are combined in chunk order.
 // Launch of a row kernel: a workgroup of ig x jg waves takes ig groups of m
 // landmarks i against every j (each wave one group and every jg-th tile of 64
 // j), so a step needs no partial sums in memory and no second launch.
@@ -33,7 +29,12 @@ struct RowPlan {
   int ig, jg;   // waves per workgroup: i-groups times shares of the j tiles
   int groups;   // workgroups
 };
+constexpr int kRowGroups = 2;   // i-groups of a row plan's workgroup at most
 
+// Work decomposition of one N x N pair sum.  Landmark i is owned by lane
+// (i mod 64) of a wave of i-block ib = i / 64; the j range is split into S
+// chunks (one workgroup each) and, inside a workgroup, over W waves.
+// Partial sums of different chunks are combined in chunk order.
 struct Plan {
   int n;        // landmarks
   int nb;       // i-blocks of 64

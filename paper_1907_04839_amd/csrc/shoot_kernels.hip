@@ -652,7 +652,6 @@ __device__ __forceinline__ double in_vgpr(double s) {
   return __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ float in_vgpr(float s) { return s; }
-constexpr int kRowGroups = 8;   // i-groups of a row workgroup at most
 
 // Sums of M rows, padded to a multiple of four (the combine halves them twice),
 // and where row k of a workgroup starts in its combined sums.

@@ -1,6 +1,7 @@
 // CPU test of which landmarks' state the wave that ends a row workgroup's step
 // loads (plan.h, row_state): the workgroup's own, which it alone stores, in every
-// plan of the row kernels and of the batched ones.
+// plan of the row kernels and of the batched ones; and of the i-groups that the row
+// kernels have room for.
 #include "plan.h"
 
 #include <algorithm>
@@ -30,6 +31,7 @@ int main() {
     for (int mode = 0; mode <= 2; ++mode) {
       const lddmm::RowPlan r = lddmm::row_plan(n, mode);
       if (r.m > 0 && !own_rows(r, n)) return 1;
+      if (r.ig > lddmm::kRowGroups) return 1;   // the kernels' LDS for combined sums
     }
   for (int n : {1, 2, 5, 6, 63, 64, 65, 255, 256, 257, 1000, 4099, 8191, 8192, 8193, 9300, 16383,
                 16384, 16385, 20001, 65536})
