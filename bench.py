@@ -33,7 +33,10 @@ if ROOT not in sys.path:
 FLOPS_PER_PAIR = {"fwd": 27, "adj": 62}
 # Planar problems (dim 2, z terms left out): forward 18, adjoint 42.
 FLOPS_PER_PAIR_PLANAR = {"fwd": 18, "adj": 42}
-# VALU instructions per pair (one exp2 is one instruction).
+# VALU instructions per pair (one exp2 is one instruction) of the pair loops above 5120
+# landmarks, the ones the issue ceiling is for.  The kernels of smaller problems are
+# held to the same counts; theirs, with a tile's addresses and masks, are 21 and 43 per
+# pair at 4096 landmarks (36 of the 43 are the pair's; profiles/valu_counters_pair_kernels.txt).
 VALU_PER_PAIR = {"fwd": 17, "adj": 38}
 # Point flow (eq. 4), per point-landmark pair: 3 sub, |d|^2 (1 mul + 2 FMA),
 # one exp2, 3 FMA = 15 flops in 10 VALU instructions.

@@ -237,8 +237,9 @@ lddmm_status lddmm_solve(lddmm_ctx* ctx, const lddmm_params* params, const lddmm
  * optimiser step through batched pair-sum launches replayed from a captured
  * hipGraph; jobs join at the next round after admission and leave when their
  * optimiser finishes.  A job's result does not depend on the other jobs in
- * the batch (same decomposition, same summation order, which follow from its
- * n and the server's max_slots and max_n).  All jobs of a server share T, the
+ * the batch (same decomposition, same summation order).  Those follow from its
+ * n and the server's precision, max_slots and max_n: servers of another size may
+ * differ at rounding level.  All jobs of a server share T, the
  * precision and the integrator; each job may be planar (lddmm_params.dim = 2)
  * or 3D, and takes the energy term at t = 0. */
 typedef struct lddmm_server lddmm_server;

@@ -181,9 +181,9 @@ constexpr int batch_waves(bool compensated) { return compensated ? 12 : 8; }
 // Launch shapes of a batch of at most max_slots jobs with n <= max_n:
 // stage (max_n/256, max_slots), loss max_slots.  Pair kernels: `blocks`, capacity
 // workgroups, one per (job, i-block) item, those beyond the items exit; else at
-// most kBatchGrid workgroups that share the items (job, workgroup of its row plan).  items holds nitems[0] items of 3D
-// jobs followed by nitems[1] items of planar jobs; the pair launch for dim 3
-// (or 2) takes its group.
+// most kBatchGrid workgroups that share the items (job, workgroup of its row
+// plan).  items holds nitems[0] items of 3D jobs followed by nitems[1] items of
+// planar jobs; the pair launch for dim 3 (or 2) takes its group.
 hipError_t launch_stage_batch(int mode, const BatchJob* jobs, int max_slots, int max_n,
                               hipStream_t s);
 // stage: 0 for an Euler step, else the Runge-Kutta stage (1..4) of step t;

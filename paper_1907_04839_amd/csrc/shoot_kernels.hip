@@ -23,7 +23,8 @@
 //    one workgroup per i-block would not fill the chip, over S workgroups.
 //    Partials are combined in a fixed order (waves through LDS, workgroups
 //    through a [S][C][N] buffer): no float atomics, so results are
-//    bit-reproducible and depend only on N, never on what else is running.
+//    bit-reproducible and depend only on N and the precision (a served job's also on
+//    its server's configuration), never on what else is running.
 //  * Precision modes: FP32 with one running FP32 sum per wave ("naive", in the
 //    split kernels); FP32 with FP32 sums of at most 72 pairs folded into FP64
 //    ("compensated", and both FP32 modes of the other kernels); or everything in
@@ -579,17 +580,19 @@ __global__ __launch_bounds__(64 * W) void k_adj(AdjArgs A) {
 // wave-uniform, so a workgroup can be as small as M rows and the chip fills from
 // n = 256 M on.  Each lane's M x 2D sums are added across the wave at the end:
 // two half-exchanges leave a quarter of the values per lane, the rest of the
-// sum (16 lanes x waves) is FP64 in every mode.  With T_w = n / (64 jg) <= 10
-// terms per lane the FP32 sums are short enough to need no tiles; both FP32
+// sum (16 lanes x waves) is FP64 in every mode.  A lane adds n / (64 jg) <= 18 pairs
+// (row_plan), so an FP32 sum covers kTile at most and needs no tiles; both FP32
 // modes run the same code.
 // The adjoint is written on w = a_j + e p_j: pi + s e = a_i.p_j + p_i.w and B's
 // term is g w, and A1 / kappa and -A2 share one accumulator (p_j / kappa is formed
 // once per tile): 35 VALU + 1 exp per pair and 6 sums per row instead of 37 + 1
-// and 9.
+// and 9.  The rounding of p_j / kappa costs less than the shorter sums gain: rms error
+// of dL/dq0 0.78 of the split kernels', of dL/dp0 0.72 (means over n = 4 to 5120, both
+// FP32 modes, planar and 3D, Euler and Runge-Kutta; no case above 1.1).
 // What bounds them: at n = 1000 a step takes 4.7 us, of which 3.6 are a
 // dependent launch that loads, combines and stores (n = 64 takes as long); at n =
-// 4096 the loops (12.4 and 17.9 us per step against 10.2 and 16.3 at the rate of
-// the 65536-landmark kernels).
+// 4096 the loops (10.7 and 18.3 us per step, 6.0 and 12.0 at the rate of the
+// 65536-landmark kernels: a tile's addresses and masks, four waves per SIMD).
 template <typename R>
 using Vec3 = R __attribute__((ext_vector_type(3)));
 
@@ -1099,7 +1102,7 @@ __global__ __launch_bounds__(64 * kChainWaves) void k_adj_chain(ChainArgs C, Adj
 // landmark in scalar registers 6 of the pair's 9 have one.  9 VALU + 1 exp per
 // pair; two points per lane halve the LDS reads per pair (25 cycles of a SIMD's
 // share of the LDS with one, against 37 of issue).  What bounds it is issue: on
-// the 64^3 grid around 4096 landmarks a step takes 242 us, 35 cycles per pair and
+// the 64^3 grid around 4096 landmarks a step takes 240 us, 35 cycles per pair and
 // wave, against 30 if every instruction found a partner and 40 (276 us) with
 // scalar operands.
 constexpr int kFlowTile = 64;
@@ -1762,10 +1765,11 @@ __device__ __forceinline__ AdjArgs batch_adj_args(const BatchJob& b, int t, int 
 // Work items: nitems[0] items of 3D jobs, then nitems[1] items of planar jobs;
 // the D = 3 instance takes the first group, the D = 2 instance the second.  An
 // item is one workgroup's rows of a job (row kernels); workgroup b of G takes the
-// items b, b + G, ...  The items come with the largest jobs first, so what is
-// left to balance at the end are short ones; the state is loaded after the sums
-// (other workgroups cover its latency, and the registers are worth more).  FP32's
-// occupancy is what its registers allow without spills.  What bounds it: issue.
+// items b, b + G, ... (one each, up to kBatchGrid of them).  The items come with the
+// largest jobs first, so what is left to balance at the end are short ones; the state
+// is loaded after the sums (other workgroups cover its latency, and the registers are
+// worth more).  FP32's occupancy is what its registers allow without spills.  What
+// bounds it: issue.
 template <typename R, int D, bool ADJ, bool RKS>
 __global__ __launch_bounds__(64 * kBatchWaves,
                              sizeof(R) == 8 ? 1 : ADJ ? 4 : 5) void k_batch(const BatchJob* __restrict__ J,
