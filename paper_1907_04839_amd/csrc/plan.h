@@ -188,17 +188,18 @@ constexpr int kChainMax = 64;
 //     1000: 8 0.78 | 0.54, 12 0.99 | 0.60, 16 1.13 | 0.67, 32 1.31 | 0.86
 //     2000: 1 0.37, 8 0.94 | 0.50, 12 0.91 | 0.60, 16 1.07 | 0.68, 32 1.2 | 0.95
 //     4096: 1 0.46, 8 0.95 | 0.60, 12 1.02 | 0.74, 16 1.05 | 0.84
-//     8000: 1 0.67, 4 1.01 | 0.70, 8 1.04 to 1.08 | 0.78 (0.74 of 500 to 8000), 12
-//       1.08 | 0.88;  12000: 1 0.78, 5 1.02 | 0.78;  16000: 1 1.01, 4 1.07 | 0.93
-//     16384 (its blocks alone fill the 256 CUs): 1 1.15, 2 1.10;  65536: 1 1.11
+//     8000: 1 0.67, 4 1.01 | 0.70, 8 1.00 to 1.08 | 0.78 (0.74 of 500 to 8000), 12
+//       1.08 | 0.88;  12000: 1 0.78, 5 1.02 | 0.78;  15000: 1 0.87, 2 0.97, 4 0.97 | 0.87
+//     15500 (from here one job's blocks fill the 256 CUs): 1 0.97, 2 1.05, 4 1.02 | 0.91
+//     16000: 1 1.01, 4 1.07 | 0.93;  16384: 1 1.15, 2 1.10;  65536: 1 1.11
 //   Runge-Kutta stages the same within 0.04; planar never above 0.96 up to 16000.
 //   FP64  1000: 16 slots 0.85 | 0.51, 24 0.95 | 0.57, 32 1.29 | 0.64;  4096: 16 0.95 |
 //     0.66;  8000: 8 0.92 | 0.64, 12 1.02 | 0.75, 16 1.06;  16384: 4 0.93;  65536: 0.97
 // Both sides of the lines lose something: eight equal jobs of 8000, whose blocks
-// happen to fill two rounds, against uneven ones there.
+// happen to fill two rounds, against uneven ones there (5400: 12 slots 1.04 | 0.78).
 inline bool batch_blocks(int max_slots, int max_n, int mode) {
   const bool f64 = mode == kFP64;
-  return max_slots > (f64 ? 24 : 12) || (!f64 && max_n >= 16384) ||
+  return max_slots > (f64 ? 24 : 12) || (!f64 && max_n > 15000) ||
          (long long)max_slots * ((max_n + 63) / 64) > 1024;
 }
 

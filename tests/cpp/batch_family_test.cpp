@@ -10,7 +10,7 @@ struct Case { int slots, max_n, mode; bool blocks; };
 int main() {
   const int c = lddmm::kFP32Comp, s = lddmm::kFP32, d = lddmm::kFP64;
   const Case cases[] = {
-      {1, 2000, c, false},  {1, 16383, c, false}, {1, 16384, c, true},  {2, 16384, c, true},
+      {1, 2000, c, false},  {4, 15000, c, false}, {2, 15500, c, true},  {1, 16384, c, true},  {2, 16384, c, true},
       {1, 32768, c, true},  {2, 32768, c, true},  {1, 65536, c, true},  {12, 500, c, false},
       {12, 1000, c, false}, {12, 2000, c, false}, {8, 4096, c, false},  {4, 8000, c, false},
       {8, 8000, c, false},  {32, 500, c, true},   {16, 1000, c, true},  {32, 1000, c, true},
