@@ -352,8 +352,10 @@ lddmm_status lddmm_ctx_check(lddmm_ctx* ctx, void* stream);
  * forward and of the adjoint pair-sum kernel and of the point-flow kernel
  * carries two HIP events of the call's stream (the stream the kernel runs
  * on), tied by hipExtLaunchKernel to the start and the end of the kernel's
- * execution; durations accumulate until read.  The results are the same as
- * with timing off.  Off by default.  Errors: EINVAL. */
+ * execution; durations accumulate until read.  Up to 64 landmarks one launch
+ * takes all steps of a pass (at most 4096); launches that only add partial
+ * sums (of a split step, of a velocity spread over workgroups) carry none.
+ * The results are the same as with timing off.  Off by default.  Errors: EINVAL. */
 typedef struct {
   double fwd_ms;           /* summed duration of forward pair-kernel launches */
   double adj_ms;           /* summed duration of adjoint pair-kernel launches */
